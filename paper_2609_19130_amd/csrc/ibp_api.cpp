@@ -56,6 +56,13 @@ struct ibp_plan_s {
   bool zsmall = false;                 // general z transform in the small tile
   bool xsmall = false;                 // general x transform in the small tile
   bool xwide = true, zwide = true;     // general transform needs the wide kernel family
+  // FP64 matrix-product transforms (S = 0: off) and their tiles
+  // (set_mdft_split)
+  MdftShape mx, mz;
+  mdft::XExtra mxf{}, mxi{};   // R2C, C2R
+  int mzlc = 0, mzRS = 0;
+  int cus = 256;   // compute units of the device
+  int zdiv = 1;
   // fused persistent x/z passes (nz = nx and both lengths register-FFT sizes)
   bool fused = false;
   int fblocks64 = 0, fblocks32 = 0;   // persistent blocks (FP64 / FP32 spectrum)
@@ -192,6 +199,74 @@ bool z_small(const FftPlan& fpz, int nz) {
   return fpz.any ? nz + 1 <= kTileZ64s / 2 : nz <= kTileZ64s;
 }
 
+mdft::Plan mdft_plan(const MdftShape& m) { return mdft::Plan{m.S, m.P, m.MT, m.KT}; }
+
+// Rows (pairs) per tile, `points` tasks and `per` LDS columns each: as many as
+// possible in flight on a compute unit, weighted by how full the 16-column
+// products are (384-point rows at 384 x 256 x 320: 10 pairs, two blocks of
+// four waves, 4.3 TB/s against 3.4 for 6 pairs, two blocks of three), but
+// few enough for a tile on every compute unit (`rows` of them in the grid).
+template <typename Lds>
+int mdft_rows(int S, int points, int per, size_t lim, long rows, int cus, Lds lds) {
+  const int most = mdft::max_threads(S) * mdft::tasks_per_thread(S);
+  int best = 1;
+  double best_score = 0.0;
+  for (int r = 1; r == 1 || (r * points <= most && lds(r * per | 1, r) <= lim); ++r) {
+    const size_t bytes = lds(r * per | 1, r);
+    const int nt = mdft::block_threads(S, r * points, bytes), cols = (r * per + 15) / 16 * 16;
+    if (nt > mdft::max_threads(S)) break;
+    if (r > 1 && rows < (long)r * cus) break;
+    const double score = (double)mdft::blocks_per_cu(S, nt, bytes) * r * (r * per) / cols;
+    if (score > best_score * 1.02) {
+      best = r;
+      best_score = score;
+    }
+  }
+  return best;
+}
+
+// LDS row stride of 2^lc columns: neighbouring rows C = 2^lc values apart in
+// the 16 that an LDS access serves.
+int mdft_z_stride(int S, int lc) {
+  const int C = 1 << lc;
+  int rs = S << lc;
+  while (rs % 16 != C % 16) ++rs;
+  return rs;
+}
+
+// Tiles of the matrix-product transforms (zdiv 2 and more: half lines in z; the
+// general kernels' tile choices do not apply to them).
+void set_mdft_split(ibp_plan_s* p) {
+  if (p->mx.S) {
+    const int S = p->mx.S, P = p->mx.P, kh = 1 + 2 * (S / 2);
+    const mdft::Plan M = mdft_plan(p->mx);
+    const size_t lim = mdft::kMaxLds;
+    const long rows = (long)p->ny * p->nz;
+    p->mxf.M = p->mxi.M = M;
+    p->mxf.cus = p->mxi.cus = p->cus;
+    p->mxf.RP = mdft_rows(S, P, kh, lim, (rows + 1) / 2, p->cus, [&](int rs, int) { return mdft::lds_r2c(M, rs); });
+    p->mxf.RS = (p->mxf.RP * kh) | 1;
+    p->mxi.RP = mdft_rows(S, P / 2 + 1, S, lim, rows, p->cus, [&](int rs, int rp) { return mdft::lds_c2r(M, rs, rp); });
+    p->mxi.RS = (p->mxi.RP * S) | 1;
+  }
+  if (p->mz.S) {
+    const int S = p->mz.S, P = p->mz.P;
+    const mdft::Plan M = mdft_plan(p->mz);
+    auto fits = [&](int lc) {
+      return mdft::lds_z(M, mdft_z_stride(S, lc)) <= mdft::kMaxLds && (P << lc) <= mdft::max_threads(S) * mdft::tasks_per_thread(S);
+    };
+    // whole 128-byte lines (632 x 1263 x 632: 2.4 ms a pass with half lines and
+    // two blocks per compute unit, 1.8 with whole lines and one), and an odd S
+    // two of them, which fill the 16-column products; half lines where those
+    // do not fit
+    int lc = S % 2 ? 4 : 3;
+    while (lc > 2 && !fits(lc)) --lc;
+    if (p->zdiv > 1) lc = 2;
+    p->mzlc = lc;
+    p->mzRS = mdft_z_stride(S, lc);
+  }
+}
+
 // The FP64 and FP32 half spectra are separate regions: the FP64 inverse
 // passes of IBP_MIXED_F64INV read the FP32 one and write the FP64 one.
 // x-pass rows per block and block counts for the plan's x tile (small or
@@ -209,10 +284,13 @@ void set_x_split(ibp_plan_s* p) {
   }
   p->nb64 = (nrows + p->rb64 - 1) / p->rb64;
   p->nb32 = (nrows + p->rb32 - 1) / p->rb32;
+  set_mdft_split(p);
 }
 
 // z-pass columns per block for the plan's z tile, divided by zdiv.
 void set_z_split(ibp_plan_s* p, int zdiv) {
+  p->zdiv = zdiv;
+  set_mdft_split(p);
   p->zc64max = z_tile_cols(p, p->zsmall ? kTileZ64s : kTileZ64);
   p->zc32max = z_tile_cols(p, p->zsmall ? kTileZ32s : kTileZ32);
   p->zc64max = std::min(std::min(p->zc64max, 64), p->hp);
@@ -558,6 +636,13 @@ ibp_status_t ibp_plan_create(ibp_plan_t* out, int nx, int ny, int nz, double Lx,
     // the general kernels' transform length (nx/2 pairs, or nx when odd)
     p->xbm = reg_bluestein_length(fpx, nx, 1024);
     p->zbm = nz > 1 ? reg_bluestein_length(fpz, nz, 1024) : 0;
+    // FP64 lines without register power-of-two kernels: matrix products
+    // (IBP_MDFT=0 turns them off, for comparison runs)
+    const char* md = getenv("IBP_MDFT");
+    if (md == nullptr || atoi(md) != 0) {
+      if (!rfft::supported(p->h) && nx <= 2048) p->mx = mdft_shape(nx);
+      if (!rfft::supported(nz) && nz <= 1024) p->mz = mdft_shape(nz);
+    }
     ytri_shape(ny, &p->yP, &p->yK);
     p->xfast = rfft::supported(p->h);
     p->zfast = rfft::supported(nz);
@@ -688,6 +773,7 @@ ibp_status_t ibp_plan_create(ibp_plan_t* out, int nx, int ny, int nz, double Lx,
     }
 
     hipError_t e = hipGetDevice(&p->device);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&p->cus, hipDeviceAttributeMultiprocessorCount, p->device);
     if (e == hipSuccess && p->fused) {
       int cus = 0, b64 = 0, b32 = 0;
       e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device);
@@ -746,6 +832,7 @@ ibp_status_t ibp_plan_create(ibp_plan_t* out, int nx, int ny, int nz, double Lx,
       }
     }
     p->twz32 = reinterpret_cast<const Cx<float>*>(d + o_twz32);
+    set_mdft_split(p);
 
     p->ws_bytes = workspace_bytes(p);
     e = hipMalloc(&p->ws, p->ws_bytes);
@@ -1283,6 +1370,8 @@ XArgs<T> with_xblu(const ibp_plan_s* p, const XArgs<T>& a) {
 template <typename T>
 hipError_t run_xr2c(const ibp_plan_s* p, int mode, const XArgs<T>& a, hipStream_t s) {
   if (p->xfast && mode != XM_RESID_ONLY) return launch_xr2c_fast<T>(mode, a, s);
+  if constexpr (sizeof(T) == 8)
+    if (p->mx.S && (mode == XM_PLAIN || mode == XM_DIV)) return mdft::launch_xr2c(mode, a, p->mxf, s);
   // register Bluestein: the FP64 right-hand side pass (the others keep the
   // LDS kernels, whose norm partials and residual modes it does not carry)
   if constexpr (sizeof(T) == 8)
@@ -1303,6 +1392,8 @@ hipError_t run_xr2c(const ibp_plan_s* p, int mode, const XArgs<T>& a, hipStream_
 template <typename T>
 hipError_t run_xc2r(const ibp_plan_s* p, int mode, const XArgs<T>& a, hipStream_t s) {
   if (p->xfast) return launch_xc2r_fast<T>(mode, a, s);
+  if constexpr (sizeof(T) == 8)
+    if (p->mx.S) return mdft::launch_xc2r(mode, a, p->mxi, s);
   if (p->xbm && p->chunk <= 0) return launch_xblu_c2r<T>(mode, with_xblu(p, a), p->xbm, s);
   return launch_xc2r<T>(mode, p->xsmall, p->xwide, a, s);
 }
@@ -1310,6 +1401,13 @@ hipError_t run_xc2r(const ibp_plan_s* p, int mode, const XArgs<T>& a, hipStream_
 template <typename T>
 hipError_t run_zfft(const ibp_plan_s* p, bool inverse, const ZfArgs<T>& a, int nplanes, hipStream_t s) {
   if (p->zfast) return launch_zfft_fast<T>(inverse, a, nplanes, s);
+  if constexpr (sizeof(T) == 8) {
+    if (p->mz.S) {
+      const mdft::ZArgs z{a.spec, a.twz, a.ctl, mdft_plan(p->mz), a.nz, a.hp, p->mzlc,
+                          p->mzRS, a.rs, a.ps, a.check_done, a.plane0, p->cus};
+      return mdft::launch_z(inverse, z, nplanes, s);
+    }
+  }
   if (p->zbm) {
     ZfArgs<T> b = a;
     if constexpr (sizeof(T) == 8) {
@@ -1623,6 +1721,8 @@ ibp_status_t enqueue_mixed(ibp_plan_s* p, const double* rhs, double* phi, hipStr
 // covers every grid.  Per-grid arguments sit in a device table built once;
 // the line-solve coefficient tables are re-padded to the batch's common
 // lanes x rows shape (the largest ny decides it).
+constexpr int kBatchStages = 10;
+
 struct ibp_batch_s {
   int device = 0;
   int count = 0;
@@ -1632,11 +1732,13 @@ struct ibp_batch_s {
   std::vector<unsigned> gens;
   void* dmem = nullptr;
   void* desc = nullptr;      // BatchGrid<T>[count]
-  long* start = nullptr;     // [7][count + 1]: prefix offsets of the stage launches (nblk order)
-  // blocks of the x (narrow, wide family), z (narrow, wide) and y (rows per
-  // lane K, K/2, K/4) stage launches: each stage runs as several launches
-  // over the grids of one kind (a grid has no blocks in the others)
-  long nblk[7] = {0, 0, 0, 0, 0, 0, 0};
+  long* start = nullptr;     // [kBatchStages][count + 1]: prefix offsets of the stage launches (nblk order)
+  // blocks of the x (narrow, wide family), z (narrow, wide), y (rows per lane
+  // K, K/2, K/4) and matrix-product (R2C, C2R, z) stage launches: each stage
+  // runs as several launches over the grids of one kind (a grid has no blocks
+  // in the others)
+  long nblk[kBatchStages] = {0};
+  size_t mlds[3] = {0, 0, 0};   // largest tile of the R2C, C2R and z matrix-product launches
   int yKc[3] = {0, 0, 0}, yMc[3] = {0, 0, 0};   // rows per lane and columns per block of the y launches
   int yP = 32, yK = 2, yM = 8;
   int xdiv = 1, zdiv = 1;    // x rows and z columns per block: the largest tile's, divided by these
@@ -1671,9 +1773,9 @@ hipError_t persist_schedule(ibp_batch_s* b, const std::vector<BatchGrid<T>>& hd)
 template <typename T>
 hipError_t batch_apply(ibp_batch_s* b, std::vector<BatchGrid<T>>& hd) {
   const int n = b->count;
-  b->hstart.assign(7 * (n + 1), 0);
-  long* h[7];
-  for (int i = 0; i < 7; ++i) h[i] = b->hstart.data() + i * (n + 1);
+  b->hstart.assign(kBatchStages * (n + 1), 0);
+  long* h[kBatchStages];
+  for (int i = 0; i < kBatchStages; ++i) h[i] = b->hstart.data() + i * (n + 1);
   // y launches: the base shape's K, K/2, K/4 rows per lane, with columns per
   // block raised in proportion (same LDS tile, same bytes per block)
   for (int c = 0; c < 3; ++c) {
@@ -1693,16 +1795,21 @@ hipError_t batch_apply(ibp_batch_s* b, std::vector<BatchGrid<T>>& hd) {
     d.zcolblocks = (d.z.hp + zc - 1) / zc;
     const long nzb = d.z.nz > 1 ? (long)d.zcolblocks * d.y.ny : 0;
     const bool xw = b->plans[g]->xwide, zw = b->plans[g]->zwide;
-    h[0][g + 1] = h[0][g] + (xw ? 0 : nxb);
-    h[1][g + 1] = h[1][g] + (xw ? nxb : 0);
-    h[2][g + 1] = h[2][g] + (zw ? 0 : nzb);
-    h[3][g + 1] = h[3][g] + (zw ? nzb : 0);
+    const bool xm = d.md.f.M.S != 0, zm = d.md.z.M.S != 0;
+    auto blocks = [](bool on, unsigned tiles) { return on ? (long)(tiles + mdft::kBatchTiles - 1) / mdft::kBatchTiles : 0; };
+    h[0][g + 1] = h[0][g] + (xw || xm ? 0 : nxb);
+    h[1][g + 1] = h[1][g] + (xw && !xm ? nxb : 0);
+    h[2][g + 1] = h[2][g] + (zw || zm ? 0 : nzb);
+    h[3][g + 1] = h[3][g] + (zw && !zm ? nzb : 0);
+    h[7][g + 1] = h[7][g] + blocks(xm, d.md.ftiles);
+    h[8][g + 1] = h[8][g] + blocks(xm, d.md.itiles);
+    h[9][g + 1] = h[9][g] + blocks(zm, d.md.ztiles);
     for (int c = 0; c < 3; ++c) {
       const int M = b->yMc[c];
       h[4 + c][g + 1] = h[4 + c][g] + (d.yk == b->yKc[c] ? (d.y.Q + M - 1) / M + zero_blocks(d.y.ny) : 0);
     }
   }
-  for (int i = 0; i < 7; ++i) b->nblk[i] = h[i][n];
+  for (int i = 0; i < kBatchStages; ++i) b->nblk[i] = h[i][n];
   hipError_t e = hipMemcpy(b->desc, hd.data(), n * sizeof(BatchGrid<T>), hipMemcpyHostToDevice);
   if (e == hipSuccess)
     e = hipMemcpy(b->start, b->hstart.data(), b->hstart.size() * sizeof(long), hipMemcpyHostToDevice);
@@ -1733,11 +1840,13 @@ hipError_t persist_schedule(ibp_batch_s* b, const std::vector<BatchGrid<T>>& hd)
     const long nyb = (d.y.Q + M - 1) / M + zero_blocks(d.y.ny);
     const int yk = d.yk == b->yK ? PK_Y0 : (d.yk == b->yK / 2 ? PK_Y1 : PK_Y2);
     auto& v = stages[g];
-    v.push_back({PK_XR2C, 0, 0, nxb});
-    v.push_back({PK_ZF, 0, 0, nzb});
+    const bool xm = d.md.f.M.S != 0;
+    const long nz1 = d.md.z.M.S ? (long)d.md.ztiles : nzb;
+    v.push_back({PK_XR2C, 0, 0, xm ? (long)d.md.ftiles : nxb});
+    v.push_back({PK_ZF, 0, 0, nz1});
     v.push_back({yk, 0, PF_INIT, nyb});
-    v.push_back({PK_ZI, 0, 0, nzb});
-    v.push_back({PK_XC2R, 0, 0, nxb});
+    v.push_back({PK_ZI, 0, 0, nz1});
+    v.push_back({PK_XC2R, 0, 0, xm ? (long)d.md.itiles : nxb});
     if (mixed) {
       for (int k = 1; k <= b->max_iters; ++k) {
         v.push_back({PK_XRES, k, 0, nxb});
@@ -1860,6 +1969,45 @@ hipError_t persist_setup(ibp_batch_s* b) {
   return hipSuccess;
 }
 
+// Matrix-product tiles of one grid of a batch (BatchPlan), where its lengths
+// have a shape with S <= 8 whose tiles fit.
+void batch_mdft(const ibp_plan_s* p, mdft::BatchPlan& md, const ZfArgs<double>& z) {
+  const char* on = getenv("IBP_MDFT");
+  if (on && atoi(on) == 0) return;
+  const long nrows = (long)p->ny * p->nz;
+  const MdftShape x = p->nx <= 2048 ? mdft_shape(p->nx) : MdftShape{};
+  if (x.S && x.S <= 8) {
+    const mdft::Plan M = mdft_plan(x);
+    const int kh = 1 + 2 * (x.S / 2), most = kThreads * mdft::tasks_per_thread(x.S);
+    // the most rows that a block's threads and LDS hold
+    auto rows = [&](int points, auto lds) {
+      int r = 0;
+      while ((r + 1) * points <= most && lds(r + 1) <= mdft::kBatchLds && r < 64) ++r;
+      return r;
+    };
+    const int rf = rows(x.P, [&](int r) { return mdft::lds_r2c(M, (r * kh) | 1); });
+    const int ri = rows(x.P / 2 + 1, [&](int r) { return mdft::lds_c2r(M, (r * x.S) | 1, r); });
+    if (rf > 0 && ri > 0) {
+      md.f = mdft::XExtra{M, rf, (rf * kh) | 1, p->cus};
+      md.i = mdft::XExtra{M, ri, (ri * x.S) | 1, p->cus};
+      md.ftiles = (unsigned)((nrows + 2 * rf - 1) / (2 * rf));
+      md.itiles = (unsigned)((nrows + ri - 1) / ri);
+    }
+  }
+  const MdftShape zs = p->nz > 1 && p->nz <= 1024 ? mdft_shape(p->nz) : MdftShape{};
+  if (zs.S && zs.S <= 8) {
+    const mdft::Plan M = mdft_plan(zs);
+    for (int lc : {4, 3}) {
+      const int C = 1 << lc, RS = mdft_z_stride(zs.S, lc);
+      if ((zs.P << lc) > kThreads * mdft::tasks_per_thread(zs.S) || mdft::lds_z(M, RS) > mdft::kBatchLds) continue;
+      md.z = mdft::ZArgs{z.spec, z.twz, z.ctl, M, p->nz, p->hp, lc, RS, z.rs, z.ps, 0, 0, p->cus};
+      md.zgroups = (unsigned)((p->hp + C - 1) / C);
+      md.ztiles = md.zgroups * (unsigned)p->ny;
+      break;
+    }
+  }
+}
+
 template <typename T>
 ibp_status_t batch_build(ibp_batch_s* b) {
   constexpr bool kF64 = sizeof(T) == 8;
@@ -1880,7 +2028,7 @@ ibp_status_t batch_build(ibp_batch_s* b) {
   // device memory: descriptors | prefix offsets | padded a, c tables | partials
   std::vector<size_t> o_part(n);
   const size_t o_start = align256(n * sizeof(BatchGrid<T>));
-  const size_t o_tab = o_start + align256(7 * (n + 1) * sizeof(long));
+  const size_t o_tab = o_start + align256(kBatchStages * (n + 1) * sizeof(long));
   size_t bytes = o_tab + align256((size_t)n * 2 * PK * sizeof(T));
   for (int g = 0; g < n; ++g) {
     const ibp_plan_s* p = b->plans[g];
@@ -1939,6 +2087,15 @@ ibp_status_t batch_build(ibp_batch_s* b) {
     d.zero = zargs(p, 0, 0, 0, 0, 0);
     d.zero.part = part;
     d.yk = batch_grid_rows_per_lane(p->ny, b->yP, b->yK);
+    d.md = mdft::BatchPlan{};
+    if constexpr (kF64) {
+      batch_mdft(p, d.md, d.z);
+      if (d.md.f.M.S) {
+        b->mlds[0] = std::max(b->mlds[0], mdft::lds_r2c(d.md.f.M, d.md.f.RS));
+        b->mlds[1] = std::max(b->mlds[1], mdft::lds_c2r(d.md.i.M, d.md.i.RS, d.md.i.RP));
+      }
+      if (d.md.z.M.S) b->mlds[2] = std::max(b->mlds[2], mdft::lds_z(d.md.z.M, d.md.z.RS));
+    }
   }
   e = hipMemcpy(dtab, tab.data(), tab.size() * sizeof(T), hipMemcpyHostToDevice);
   if (e != hipSuccess) return from_hip(e);
@@ -1958,8 +2115,8 @@ ibp_status_t batch_enqueue(ibp_batch_s* b, const double* const* rhs, double* con
     P.phi[g] = phi[g];
   }
   const BatchGrid<T>* d = static_cast<const BatchGrid<T>*>(b->desc);
-  const long* st[7];
-  for (int i = 0; i < 7; ++i) st[i] = b->start + i * (n + 1);
+  const long* st[kBatchStages];
+  for (int i = 0; i < kBatchStages; ++i) st[i] = b->start + i * (n + 1);
   const bool mixed = b->prec == IBP_MIXED;
   for (ibp_plan_t p : b->plans) {
     p->last_stream = s;
@@ -1970,18 +2127,28 @@ ibp_status_t batch_enqueue(ibp_batch_s* b, const double* const* rhs, double* con
     IBP_HIP(launch_persist<T>(b->wide, b->yP, b->yK, b->pargs, P, b->persist_blocks, s));
     return IBP_SUCCESS;
   }
-  // each transform stage: the narrow-family launch, then the wide one
+  // each transform stage: the narrow-family launch, the wide one, then the
+  // matrix products
   auto xr2c = [&](int mode, const BatchLaunch& l) {
     hipError_t e = launch_batch_xr2c<T>(mode, b->xsmall, false, d, st[0], b->nblk[0], P, l, s);
-    return e == hipSuccess ? launch_batch_xr2c<T>(mode, b->xsmall, true, d, st[1], b->nblk[1], P, l, s) : e;
+    if (e == hipSuccess) e = launch_batch_xr2c<T>(mode, b->xsmall, true, d, st[1], b->nblk[1], P, l, s);
+    if constexpr (sizeof(T) == 8)
+      if (e == hipSuccess) e = mdft::launch_batch_xr2c(d, st[7], b->nblk[7], b->mlds[0], P, n, s);
+    return e;
   };
   auto xc2r = [&](int mode, const BatchLaunch& l) {
     hipError_t e = launch_batch_xc2r<T>(mode, b->xsmall, false, d, st[0], b->nblk[0], P, l, s);
-    return e == hipSuccess ? launch_batch_xc2r<T>(mode, b->xsmall, true, d, st[1], b->nblk[1], P, l, s) : e;
+    if (e == hipSuccess) e = launch_batch_xc2r<T>(mode, b->xsmall, true, d, st[1], b->nblk[1], P, l, s);
+    if constexpr (sizeof(T) == 8)
+      if (e == hipSuccess) e = mdft::launch_batch_xc2r(d, st[8], b->nblk[8], b->mlds[1], P, n, s);
+    return e;
   };
   auto zfft = [&](bool inverse, const BatchLaunch& l) {
     hipError_t e = launch_batch_zfft<T>(inverse, b->zsmall, false, d, st[2], b->nblk[2], l, s);
-    return e == hipSuccess ? launch_batch_zfft<T>(inverse, b->zsmall, true, d, st[3], b->nblk[3], l, s) : e;
+    if (e == hipSuccess) e = launch_batch_zfft<T>(inverse, b->zsmall, true, d, st[3], b->nblk[3], l, s);
+    if constexpr (sizeof(T) == 8)
+      if (e == hipSuccess) e = mdft::launch_batch_z(inverse, d, st[9], b->nblk[9], b->mlds[2], n, s);
+    return e;
   };
   auto ytri = [&](const BatchLaunch& l) {
     hipError_t e = hipSuccess;

@@ -205,6 +205,26 @@ struct OddConst<11> {
   }
 };
 
+template <>
+struct OddConst<13> {
+  __device__ static constexpr double c(int k) {
+    return k == 1 ? 0.8854560256532099
+         : k == 2 ? 0.5680647467311558
+         : k == 3 ? 0.12053668025532305
+         : k == 4 ? -0.3546048870425356
+         : k == 5 ? -0.7485107481711011
+                  : -0.970941817426052;
+  }
+  __device__ static constexpr double s(int k) {
+    return k == 1 ? 0.46472317204376856
+         : k == 2 ? 0.8229838658936564
+         : k == 3 ? 0.992708874098054
+         : k == 4 ? 0.9350162426854148
+         : k == 5 ? 0.6631226582407952
+                  : 0.23931566428755777;
+  }
+};
+
 template <int R, bool INV, typename T>
 struct BflyOdd {
   __device__ __forceinline__ static void run(Cx<T>* v) {
@@ -249,6 +269,8 @@ template <bool INV, typename T>
 struct Bfly<7, INV, T> : BflyOdd<7, INV, T> {};
 template <bool INV, typename T>
 struct Bfly<11, INV, T> : BflyOdd<11, INV, T> {};
+template <bool INV, typename T>
+struct Bfly<13, INV, T> : BflyOdd<13, INV, T> {};
 
 // ---------------------------------------------------------------- LDS FFT
 // One Stockham stage over all sequences.  Every thread first reads and

@@ -134,6 +134,31 @@ void twiddles(int n, std::vector<double>& re, std::vector<double>& im) {
   }
 }
 
+// ---------------------------------------------------------------- matrix-product transforms
+MdftShape mdft_shape(int n) {
+  MdftShape best;
+  double best_cost = 0.0;
+  if (n < 16) return best;
+  auto consider = [&](int S) {
+    if (n % S) return;
+    const int P = n / S, L = P / 2 + 1;
+    if (P < 4 || P > kMdftMaxP) return;
+    MdftShape m;
+    m.S = S;
+    m.P = P;
+    m.MT = (L + 15) / 16;
+    m.KT = (L + 7) / 8 * 2;
+    const double cost = 16.0 * m.MT * 4.0 * m.KT / P;
+    if (best.S == 0 || cost < best_cost) {
+      best = m;
+      best_cost = cost;
+    }
+  };
+  for (int S = 8; S >= 1; --S) consider(S);
+  for (int S = 9; S <= 16; ++S) consider(S);
+  return best;
+}
+
 // ---------------------------------------------------------------- line-solve shape
 // P = 32 lanes per column (P = 64 when ny > 384), K rows per lane from
 // {2, 4, 8, 12, 16, 24}.

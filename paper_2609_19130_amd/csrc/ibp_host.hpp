@@ -44,6 +44,18 @@ void bluestein_tables(int n, int m, std::vector<double>& chirp, std::vector<doub
 // W_n^e = exp(-2 pi i e / n), e = 0..n-1.
 void twiddles(int n, std::vector<double>& re, std::vector<double>& im);
 
+// Matrix-product transforms (ibp_mdft.hpp): n = S P with an S-point DFT in
+// registers (S <= 16) and the P-point DFT as real products of (P/2 + 1)^2
+// entries padded to MT 16-row and KT 4-deep steps (KT even).  S = 0: not taken.
+struct MdftShape {
+  int S = 0, P = 0, MT = 0, KT = 0;
+};
+// The factorisation of n with the fewest multiply-adds per value in the
+// products (among equals the largest S up to 8, whose tasks leave room for
+// three waves per SIMD, before the smallest above); S = 0 for n below 16 or
+// when every divisor S leaves P above kMdftMaxP.
+constexpr int kMdftMaxP = 256;
+MdftShape mdft_shape(int n);
 // Dimension check: kDimsOk, kDimsInvalid (a size below 1) or
 // kDimsUnsupported (outside what the kernels cover).  On success fills the
 // x (half length) and z factorisations when the pointers are non-null.

@@ -302,6 +302,65 @@ template <typename T>
 hipError_t launch_xblu_c2r(int mode, const XArgs<T>& a, int M, hipStream_t s);
 hipError_t launch_x_roundtrip(const RtArgs& a, hipStream_t s);
 
+// Matrix-product transforms (ibp_mdft.hpp) of any length n = S P: FP64 z
+// lines and x rows.
+namespace mdft {
+// Plan of one length: MT 16-row and KT 4-deep steps (an even number) cover
+// P/2 + 1.
+struct Plan {
+  int S, P;
+  int MT, KT;
+};
+
+struct ZArgs {
+  Cx<double>* spec;
+  const Cx<double>* tw;   // W_nz^e
+  const Ctl* ctl;
+  Plan M;
+  int nz, hp;
+  int lc;                 // kx columns per block: 2^lc
+  int RS;                 // LDS row stride
+  long rs, ps;            // spectrum row and plane strides (elements)
+  int check_done;
+  int plane0;
+  int cus;                // compute units of the device
+};
+
+struct XExtra {
+  Plan M;
+  int RP;    // rows per tile (C2R) or row pairs per tile (R2C)
+  int RS;    // LDS row stride
+  int cus;   // compute units of the device
+};
+
+// Block shapes, shared with the plan's choice of rows and columns per tile.
+constexpr size_t kMaxLds = 160 * 1024;
+
+// A batch's grids take the products where their tiles fit 256-thread blocks of
+// S <= 8 tasks and kBatchLds bytes of LDS (three blocks per compute unit);
+// S = 0 in a direction's plan: the general kernels.  Tiles of the R2C, C2R
+// and z passes; a staged launch gives a block kBatchTiles consecutive ones.
+constexpr size_t kBatchLds = 52 * 1024;
+constexpr int kBatchTiles = 4;
+struct BatchPlan {
+  XExtra f, i;   // R2C and C2R (M.S = 0: off)
+  ZArgs z;       // (M.S = 0: off)
+  unsigned ftiles, itiles, zgroups, ztiles;
+};
+size_t lds_z(const Plan& M, int RS);
+size_t lds_r2c(const Plan& M, int RS);
+size_t lds_c2r(const Plan& M, int RS, int RP);
+int tasks_per_thread(int S);
+int block_threads(int S, int tasks, size_t lds);
+int blocks_per_cu(int S, int threads, size_t lds);
+// Threads a block may have: the registers of S-point tasks (tasks_per_thread(S)
+// a thread) leave 128 each at 1024 threads, 168 at 768 and 256 at 512.
+__host__ __device__ constexpr int max_threads(int S) { return S <= 2 ? 1024 : S <= 8 ? 768 : 512; }
+hipError_t launch_z(bool inverse, const ZArgs& a, int nplanes, hipStream_t s);
+hipError_t launch_xr2c(int mode, const XArgs<double>& a, const XExtra& e, hipStream_t s);
+hipError_t launch_xc2r(int mode, const XArgs<double>& a, const XExtra& e, hipStream_t s);
+}  // namespace mdft
+
 struct ZeroArgs {        // FP64 (0,0) mode and solve control
   const double* rowsum;
   double* ghat;          // [ny] plane sums
@@ -375,6 +434,7 @@ struct BatchGrid {
   ZeroArgs zero;   // init, mixed, iter, final_pass replaced at launch
   int zcolblocks;  // z-pass column blocks per plane
   int yk;          // line-solve rows per lane for this grid (the batch's K, K/2 or K/4)
+  mdft::BatchPlan md;   // FP64 matrix-product transforms of this grid
 };
 
 struct BatchPtrs {
@@ -440,6 +500,15 @@ hipError_t launch_persist(bool wide, int P, int K, const PersistArgs& a, const B
                           hipStream_t s);
 
 // Stages of a batched solve; each launcher covers every grid in one launch.
+// Matrix-product stages (FP64): lds is the largest tile's bytes.
+namespace mdft {
+hipError_t launch_batch_xr2c(const BatchGrid<double>* d, const long* start, long nblocks, size_t lds,
+                             const BatchPtrs& p, int count, hipStream_t s);
+hipError_t launch_batch_xc2r(const BatchGrid<double>* d, const long* start, long nblocks, size_t lds,
+                             const BatchPtrs& p, int count, hipStream_t s);
+hipError_t launch_batch_z(bool inverse, const BatchGrid<double>* d, const long* start, long nblocks, size_t lds,
+                          int count, hipStream_t s);
+}  // namespace mdft
 template <typename T>
 hipError_t launch_batch_xr2c(int mode, bool small, bool wide, const BatchGrid<T>* d, const long* start, long nblocks, const BatchPtrs& p,
                              const BatchLaunch& l, hipStream_t s);

@@ -21,6 +21,7 @@
 // a claimed item always ends; it is also bounded, raising the grid's error
 // flag instead of hanging.
 #include "ibp_internal.hpp"
+#include "ibp_mbatch.hpp"
 #include "ibp_xz_kernels.hpp"
 #include "ibp_ytri_body.hpp"
 
@@ -41,8 +42,36 @@ struct PersistShape {
   static constexpr long bx = (long)TLX * sizeof(Cx<T>);
   static constexpr long bz = (long)(TLZ + 64) * sizeof(Cx<T>);
   static constexpr long by = ytile_slots<M, P, K0>() * (long)sizeof(Cx<T>);
-  static constexpr long buf = bx > bz ? (bx > by ? bx : by) : (bz > by ? bz : by);
+  static constexpr long bg = bx > bz ? (bx > by ? bx : by) : (bz > by ? bz : by);
+  // FP64: the matrix-product tiles too
+  static constexpr long buf = sizeof(T) == 8 && (long)mdft::kBatchLds > bg ? (long)mdft::kBatchLds : bg;
 };
+
+// One tile of a matrix-product stage.  A function of its own: its bodies are
+// then built once and not once per kernel instance.  Arguments arrive in
+// vector registers; they are the same in every lane and are made uniform
+// again (the bodies hold barriers and scalar branches).
+typedef __attribute__((address_space(3))) char lds_char;
+template <typename P>
+__device__ __forceinline__ P* uniform_ptr(P* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint64_t lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v);
+  const uint64_t hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32));
+  return reinterpret_cast<P*>(lo | hi << 32);
+}
+__device__ __noinline__ void pb_matrix(int kind_, const BatchGrid<double>* G_, const double* f_, double* phi_,
+                                       unsigned tile_, lds_char* smem) {
+  const int kind = __builtin_amdgcn_readfirstlane(kind_);
+  const unsigned tile = (unsigned)__builtin_amdgcn_readfirstlane((int)tile_);
+  const BatchGrid<double>& G = *uniform_ptr(G_);
+  Cx<double>* lds = reinterpret_cast<Cx<double>*>((char*)smem);
+  switch (kind) {
+    case PK_XR2C: mdft::batch_r2c(G, uniform_ptr(f_), tile, tile + 1, lds); break;
+    case PK_XC2R: mdft::batch_c2r(G, uniform_ptr(phi_), tile, tile + 1, lds); break;
+    case PK_ZF: mdft::batch_z<false>(G, tile, tile + 1, lds); break;
+    default: mdft::batch_z<true>(G, tile, tile + 1, lds); break;
+  }
+}
 
 // Segment of queue q holding queue position `item`: the last segment whose
 // first item is <= item (wave-uniform binary search).
@@ -109,6 +138,14 @@ __device__ __forceinline__ void persist_item(const PersistArgs& A, const BatchPt
   const BatchGrid<T>* D = static_cast<const BatchGrid<T>*>(A.grids);
   const int g = sg.g;
   Cx<T>* buf = reinterpret_cast<Cx<T>*>(smem);
+  if constexpr (sizeof(T) == 8) {
+    const mdft::BatchPlan& md = D[g].md;
+    const bool x = sg.kind == PK_XR2C || sg.kind == PK_XC2R, z = sg.kind == PK_ZF || sg.kind == PK_ZI;
+    if ((x && __builtin_amdgcn_readfirstlane(md.f.M.S)) || (z && __builtin_amdgcn_readfirstlane(md.z.M.S))) {
+      pb_matrix(sg.kind, D + g, Pt.f[g], Pt.phi[g], (unsigned)blk, (lds_char*)smem);
+      return;
+    }
+  }
   switch (sg.kind) {
     case PK_XR2C: pb_x<T, W, XM_PLAIN>(D, g, Pt.f[g], Pt.phi[g], sg.iter, blk, buf, sh); break;
     case PK_XC2R: pb_x<T, W, 10>(D, g, Pt.f[g], Pt.phi[g], sg.iter, blk, buf, sh); break;
