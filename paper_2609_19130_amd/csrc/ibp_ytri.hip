@@ -176,6 +176,8 @@ static hipError_t launch_ytri_mp(int K, const YArgs<T, U>& a, const ZeroArgs& z,
 
 template <typename T, typename U>
 hipError_t launch_ytri(int P, int K, int want, const YArgs<T, U>& a, const ZeroArgs& z, hipStream_t s) {
+  if constexpr (sizeof(T) == 8)
+    if (!want && !ycol_override() && ycol_rows(a.ny)) return launch_ycol(a, z, s);
   const int M = ytri_cols<T>(P, K, want);
   if (P == 32) {
     switch (M) {
