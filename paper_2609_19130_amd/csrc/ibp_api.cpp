@@ -199,6 +199,13 @@ bool z_small(const FftPlan& fpz, int nz) {
   return fpz.any ? nz + 1 <= kTileZ64s / 2 : nz <= kTileZ64s;
 }
 
+// The (0,0) column of an FP64 spectrum serves as the plane sums of a singular
+// solve: not after Bluestein transforms, whose error in it is relative to the
+// whole line and not to its sum (the row sums stay the direct ones there).
+bool zero_from_column(const ibp_plan_s* p, bool xdirect, bool zdirect) {
+  return p->singular() && (xdirect || !p->fpx.blu) && (p->nz == 1 || zdirect || !p->fpz.blu);
+}
+
 mdft::Plan mdft_plan(const MdftShape& m) { return mdft::Plan{m.S, m.P, m.MT, m.KT}; }
 
 // Rows (pairs) per tile, `points` tasks and `per` LDS columns each: as many as
@@ -1559,6 +1566,7 @@ ibp_status_t enqueue_solve(ibp_plan_s* p, const double* rhs, double* phi, hipStr
   YArgs<double, double> ya{p->spec64, p->lamx, p->lamz, p->ya, p->yc, p->ctl,
                            (long)p->nz * spec_row_stride<double>(p->hp), spec_row_stride<double>(p->hp),
                            spec_plane_stride<double>(p->hp, p->nz), p->ny, p->hp, 0, p->singular()};
+  ya.zcol = zero_from_column(p, p->xfast || p->mx.S, p->zfast || p->mz.S);
   IBP_LAUNCH(P_Y, launch_ytri<double, double>(p->yP, p->yK, p->ycols, ya, zargs(p, 0, 1, 0, 0, 0), s));
   return inverse_zx<double>(p, xa, CM_SET, P_XC2R, za, s);
 }
@@ -1806,7 +1814,7 @@ hipError_t batch_apply(ibp_batch_s* b, std::vector<BatchGrid<T>>& hd) {
     h[9][g + 1] = h[9][g] + blocks(zm, d.md.ztiles);
     for (int c = 0; c < 3; ++c) {
       const int M = b->yMc[c];
-      h[4 + c][g + 1] = h[4 + c][g] + (d.yk == b->yKc[c] ? (d.y.Q + M - 1) / M + zero_blocks(d.y.ny) : 0);
+      h[4 + c][g + 1] = h[4 + c][g] + (d.yk == b->yKc[c] ? (d.y.Q + M - 1) / M + zero_blocks(d.y) : 0);
     }
   }
   for (int i = 0; i < kBatchStages; ++i) b->nblk[i] = h[i][n];
@@ -1837,7 +1845,7 @@ hipError_t persist_schedule(ibp_batch_s* b, const std::vector<BatchGrid<T>>& hd)
     const BatchGrid<T>& d = hd[g];
     const long nxb = (d.x.nrows + d.x.rows_per_block - 1) / d.x.rows_per_block;
     const long nzb = d.z.nz > 1 ? (long)d.zcolblocks * d.y.ny : 0;
-    const long nyb = (d.y.Q + M - 1) / M + zero_blocks(d.y.ny);
+    const long nyb = (d.y.Q + M - 1) / M + zero_blocks(d.y);
     const int yk = d.yk == b->yK ? PK_Y0 : (d.yk == b->yK / 2 ? PK_Y1 : PK_Y2);
     auto& v = stages[g];
     const bool xm = d.md.f.M.S != 0;
@@ -2094,6 +2102,7 @@ ibp_status_t batch_build(ibp_batch_s* b) {
         b->mlds[0] = std::max(b->mlds[0], mdft::lds_r2c(d.md.f.M, d.md.f.RS));
         b->mlds[1] = std::max(b->mlds[1], mdft::lds_c2r(d.md.i.M, d.md.i.RS, d.md.i.RP));
       }
+      d.y.zcol = zero_from_column(p, d.md.f.M.S != 0, d.md.z.M.S != 0);
       if (d.md.z.M.S) b->mlds[2] = std::max(b->mlds[2], mdft::lds_z(d.md.z.M, d.md.z.RS));
     }
   }

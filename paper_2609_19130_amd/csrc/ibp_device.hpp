@@ -502,6 +502,22 @@ __device__ __forceinline__ void block_reduce(double (&v)[NV], const bool (&is_ma
   __syncthreads();
 }
 
+// ---------------------------------------------------------------- batched launches
+// Grid of block b of a batched launch: the largest g with start[g] <= b
+// (start ascending, start[0] = 0).  64 entries a load; every wave calls it
+// with all its lanes.
+__device__ __forceinline__ int batch_grid_of(const long* start, int count, long b) {
+  int g = -1;
+  for (int i0 = 0; i0 < count; i0 += kWave) {
+    const int i = i0 + (int)(threadIdx.x & (kWave - 1));
+    const bool at_or_below = i < count && start[i] <= b;
+    const int n = __popcll(__ballot(at_or_below));
+    g += n;
+    if (n < kWave) break;
+  }
+  return g;
+}
+
 // ---------------------------------------------------------------- XCD-local scheduling
 // Hardware id of the XCD (accelerator complex die) this wave runs on: bits
 // [3:0] of the XCC_ID hardware register (register 20 on CDNA3/CDNA4).

@@ -257,6 +257,9 @@ struct YArgs {
   Cx<double>* out64;
   long out_rs, out_ps;
   int add_iter = 0;
+  // FP64, singular: the (0,0) mode takes its plane sums from the spectrum's
+  // (0,0) column instead of the row sums (zero_mode_column)
+  int zcol = 0;
 };
 
 // IBP_MIXED_F64INV, first correction without the initial iterate: the FP64
@@ -530,6 +533,8 @@ int batch_grid_rows_per_lane(int ny, int P, int K);
 // Blocks that run the FP64 (0,0) mode at the start of a grid's line-solve launch.
 constexpr int kZeroBlocks = 8;
 __host__ __device__ inline int zero_blocks(int ny) { return ny < kZeroBlocks ? ny : kZeroBlocks; }
+template <typename T, typename U>
+__host__ __device__ inline int zero_blocks(const YArgs<T, U>& a) { return a.zcol ? 1 : zero_blocks(a.ny); }
 
 struct DivArgs {          // f = (D u - q) * scale; q may be null
   const double* u;

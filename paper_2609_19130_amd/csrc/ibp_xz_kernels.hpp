@@ -291,15 +291,6 @@ __global__ __launch_bounds__(kThreads) void k_zfft(ZfArgs<T> A) {
 // Per-grid arguments are copied from the device table into registers, except
 // the FFT plans: the stage loops index them at run time, so they are read
 // from the table in place (a private copy would live in scratch memory).
-__device__ __forceinline__ int batch_grid_of(const long* start, int count, long b) {
-  int lo = 0, hi = count - 1;   // largest g with start[g] <= b
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (__builtin_amdgcn_readfirstlane((int)(start[mid] <= b))) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
 template <typename T, int MODE, int TILE, bool WIDE>
 __global__ __launch_bounds__(kThreads) void kb_xr2c(const BatchGrid<T>* __restrict__ D, const long* __restrict__ start,
                                                      BatchPtrs P, BatchLaunch L) {

@@ -34,14 +34,19 @@ __global__ __launch_bounds__(kYcolWaves * kWave) __attribute__((amdgpu_waves_per
 void k_ycol(YArgs<double, double> A, ZeroArgs Z) {
   constexpr int PW = kWave / M, NTAB = (K + M - 1) / M;   // partitions of a wave; table rows per thread
   constexpr int nw = kYcolWaves, nthreads = nw * kWave;
-  // the coefficients: (a, c) of row p K + i at p (K + 1) + i
-  __shared__ Cx<double> tab[nw * PW * (K + 1)];
+  // the coefficients: (a, c) of row p K + i at p (K + 1) + i (or the (0,0)
+  // mode's three values a row)
+  constexpr int kRows = nw * PW * K;
+  __shared__ Cx<double> tab[nw * PW * (K + 1) > 3 * kRows / 2 ? nw * PW * (K + 1) : 3 * kRows / 2];
   // the waves' composites: [wave][value][column]
   __shared__ double ex1[nw * 4 * M], ex2[nw * 3 * M], ex3[nw * 3 * M];
-  const int nzb = zero_blocks(A.ny);
+  const int nzb = zero_blocks(A);
   long lb = blockIdx.x;
   if (lb < nzb) {   // the first blocks: FP64 (0,0) mode
-    zero_mode_part<nthreads>(Z, (int)lb, nzb);
+    if (A.zcol)
+      zero_mode_column<nthreads>(Z, A.spec, A.ps, reinterpret_cast<double*>(tab));
+    else
+      zero_mode_part<nthreads>(Z, (int)lb, nzb);
     return;
   }
   lb -= nzb;
@@ -224,7 +229,7 @@ void k_ycol(YArgs<double, double> A, ZeroArgs Z) {
     d[i] = cadd(d[i], cscale(nxt, r[i]));
     nxt = d[i];
   }
-  if (!valid) return;
+  if (!valid || (zero && A.zcol)) return;
   Cx<double>* p = A.spec + (size_t)s * A.ps + col;
 #pragma unroll
   for (int i = 0; i < K; ++i) {
@@ -236,7 +241,7 @@ void k_ycol(YArgs<double, double> A, ZeroArgs Z) {
 template <int M, int K>
 static hipError_t launch_ycol_mk(const YArgs<double, double>& a, const ZeroArgs& z, hipStream_t s) {
   if (kYcolWaves * (kWave / M) * K < a.ny || a.rs % 8 != 0 || a.Q % a.rs != 0) return hipErrorInvalidValue;
-  const long nb = a.Q / M + zero_blocks(a.ny);   // + the (0,0)-mode blocks
+  const long nb = a.Q / M + zero_blocks(a);   // + the (0,0)-mode blocks
   hipLaunchKernelGGL((k_ycol<M, K>), dim3((unsigned)nb), dim3(kYcolWaves * kWave), 0, s, a, z);
   return hipGetLastError();
 }

@@ -153,7 +153,7 @@ static hipError_t launch_ytri_mpk(const YArgs<T, U>& a, const ZeroArgs& z, hipSt
   // only shapes ytri_shape and ytri_cols can select are instantiated
   if constexpr (ytile_slots<M, P, K>() * (long)sizeof(Cx<T>) <= kYTileBytes && M * P <= 512 &&
                 ytri_pair_used(P, K)) {
-    const long nb = (a.Q + M - 1) / M + zero_blocks(a.ny);   // + the (0,0)-mode blocks
+    const long nb = (a.Q + M - 1) / M + zero_blocks(a);   // + the (0,0)-mode blocks
     hipLaunchKernelGGL((k_ytri<T, U, M, P, K>), dim3((unsigned)nb), dim3(M * P), 0, s, a, z);
     return hipGetLastError();
   } else {
@@ -247,21 +247,12 @@ hipError_t launch_ytri_out64(int P, int K, const YArgs<float, double>& a, const 
 }
 
 // ---------------------------------------------------------------- batched
-__device__ __forceinline__ int ybatch_grid_of(const long* start, int count, long b) {
-  int lo = 0, hi = count - 1;   // largest g with start[g] <= b
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (__builtin_amdgcn_readfirstlane((int)(start[mid] <= b))) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
 template <typename T, int M, int P, int K>
 __global__ __launch_bounds__(M * P) __attribute__((amdgpu_waves_per_eu(ytri_waves<T>())))
 void kb_ytri(const BatchGrid<T>* __restrict__ D, const long* __restrict__ start,
                                                  BatchLaunch L) {
   __shared__ Cx<T> tile[ytile_slots<M, P, K>()];
-  const int g = ybatch_grid_of(start, L.count, blockIdx.x);
+  const int g = batch_grid_of(start, L.count, blockIdx.x);
   YArgs<T, T> a = D[g].y;
   a.check_done = L.check_done;
   ZeroArgs z = D[g].zero;

@@ -67,7 +67,7 @@ __device__ __forceinline__ double wave_excl_scan(double v) {
   return lane > 0 ? e : 0.0;
 }
 
-// Scans of the (0,0) mode over the plane sums ghat[0..ny), run by one wave
+// Scans of the (0,0) mode over the plane sums gh[0..ny), run by one wave
 // (so the result does not depend on the size of the block that runs it).
 // Lane l owns rows [l CH, l CH + CH).  Each sweep re-reads its rows' plane
 // sums (L2-resident) and recomputes the earlier sweeps' per-row values in the
@@ -75,17 +75,18 @@ __device__ __forceinline__ double wave_excl_scan(double v) {
 // registers would count for every block of the line-solve kernels that carry
 // this path.  `p`: reduced norm partials of the right-hand side pass (used
 // when Z.init).
-__device__ __forceinline__ void zero_mode_scans(const ZeroArgs& Z, const double (&p)[kPartStride]) {
+template <typename G, typename D>
+__device__ __forceinline__ void zero_mode_scans(const ZeroArgs& Z, const double (&p)[kPartStride], G gh, D dyf,
+                                                D dyc) {
   const int lane = threadIdx.x & (kWave - 1), ny = Z.ny;
   const int CH = (ny + kWave - 1) / kWave;
   const int j0 = lane * CH;
   const int j1 = j0 + CH < ny ? j0 + CH : ny;
-  const volatile double* gh = Z.ghat;            // written by other blocks of this launch
   double wsum = 0.0, dsum = 0.0, bad = 0.0;
   for (int j = j0; j < j1; ++j) {
     const double v = gh[j];
-    wsum += Z.dyf[j] * v;
-    dsum += Z.dyf[j];
+    wsum += dyf[j] * v;
+    dsum += dyf[j];
     if (!isfinite(v)) bad += 1.0;
   }
   wsum = wave_total(wsum);
@@ -96,7 +97,7 @@ __device__ __forceinline__ void zero_mode_scans(const ZeroArgs& Z, const double 
   const double mz = m * nxnz;
   // g_j = ghat_j - m nx nz; flux at the lower face of every cell of the chunk
   double loc = 0.0;
-  for (int j = j0; j < j1; ++j) loc += Z.dyf[j] * (gh[j] - mz);
+  for (int j = j0; j < j1; ++j) loc += dyf[j] * (gh[j] - mz);
   const double flux0 = wave_excl_scan(loc);
   // t_j = dyc_j flux_j (0 at the wall), summed per chunk
   double tl = 0.0;
@@ -104,8 +105,8 @@ __device__ __forceinline__ void zero_mode_scans(const ZeroArgs& Z, const double 
     double flux = flux0;
     for (int j = j0; j < j1; ++j) {
       const double fj = flux;
-      flux += Z.dyf[j] * (gh[j] - mz);
-      tl += j > 0 ? Z.dyc[j] * fj : 0.0;
+      flux += dyf[j] * (gh[j] - mz);
+      tl += j > 0 ? dyc[j] * fj : 0.0;
     }
   }
   const double X0 = wave_excl_scan(tl);
@@ -115,9 +116,9 @@ __device__ __forceinline__ void zero_mode_scans(const ZeroArgs& Z, const double 
     double flux = flux0, X = X0;
     for (int j = j0; j < j1; ++j) {
       const double fj = flux;
-      flux += Z.dyf[j] * (gh[j] - mz);
-      X += j > 0 ? Z.dyc[j] * fj : 0.0;
-      xw += Z.dyf[j] * X;
+      flux += dyf[j] * (gh[j] - mz);
+      X += j > 0 ? dyc[j] * fj : 0.0;
+      xw += dyf[j] * X;
     }
   }
   xw = wave_total(xw);
@@ -126,8 +127,8 @@ __device__ __forceinline__ void zero_mode_scans(const ZeroArgs& Z, const double 
     double flux = flux0, X = X0;
     for (int j = j0; j < j1; ++j) {
       const double fj = flux;
-      flux += Z.dyf[j] * (gh[j] - mz);
-      X += j > 0 ? Z.dyc[j] * fj : 0.0;
+      flux += dyf[j] * (gh[j] - mz);
+      X += j > 0 ? dyc[j] * fj : 0.0;
       const double v = Z.singular ? X - xbar : 0.0;
       Z.phi00[j] = Z.phi00_add ? Z.phi00[j] + v : v;
     }
@@ -187,8 +188,33 @@ __device__ __forceinline__ void zero_mode_part(const ZeroArgs& Z, int b, int nzb
 #pragma unroll
   for (int q = 0; q < kPartStride; ++q) p[q] = 0.0;
   if (Z.init) reduce_parts<NT>(Z, sh, p);
-  if (wave == 0) zero_mode_scans(Z, p);
+  // the sums were written by other blocks of this launch
+  if (wave == 0) zero_mode_scans(Z, p, static_cast<const volatile double*>(Z.ghat), Z.dyf, Z.dyc);
   if (threadIdx.x == 0) atomicExch(Z.ticket, 0);
+}
+
+// The (0,0) mode of an FP64 singular solve by one block: the plane sums are
+// the spectrum's (0,0) column (column 0), which the block zeroes for the
+// inverse transforms; the column's own solve does not store it.  No block
+// waits for another, so none needs a device-wide fence (a write-back of its
+// XCD's L2).  us, before -> after: line solve of 64 x 300 x 64 25.0 -> 15.8, whole solve
+// of 32^3 22.9 -> 19.5, line solves of 64 uneven grids batched 760 -> 459 (with
+// batch_grid_of's one load in place of six dependent ones).
+// lds: 3 ny values.
+template <int NT>
+__device__ __forceinline__ void zero_mode_column(const ZeroArgs& Z, Cx<double>* spec, long ps, double* lds) {
+  const int ny = Z.ny;
+  double *const gh = lds, *const dyf = lds + ny, *const dyc = lds + 2 * ny;
+#pragma unroll 4
+  for (int j = threadIdx.x; j < ny; j += NT) {
+    gh[j] = gld(gbl(spec) + j * ps).x;
+    dyf[j] = gbl(Z.dyf)[j];
+    dyc[j] = gbl(Z.dyc)[j];
+  }
+  __syncthreads();
+  for (int j = threadIdx.x; j < ny; j += NT) gst(gbl(spec) + j * ps, Cx<double>{0.0, 0.0});
+  const double p[kPartStride] = {};
+  if (threadIdx.x < kWave) zero_mode_scans<const double*, const double*>(Z, p, gh, dyf, dyc);
 }
 
 // ---------------------------------------------------------------- line solves
@@ -287,8 +313,15 @@ __device__ __forceinline__ void ytri_body(const YArgs<T, U>& A, const ZeroArgs& 
                                           bool kx_major = false) {
   constexpr int NT = M * P;
   if (A.check_done && __builtin_amdgcn_readfirstlane(A.ctl->done)) return;
-  const int nzb = zero_blocks(A.ny);
+  const int nzb = zero_blocks(A);
   if (blk < nzb) {   // the first blocks: FP64 (0,0) mode
+    if constexpr (sizeof(T) == 8 && sizeof(U) == 8) {
+      static_assert(sizeof(Cx<T>) * ytile_slots<M, P, K>() >= 3 * sizeof(double) * P * K, "the plane values fit the tile");
+      if (A.zcol) {
+        zero_mode_column<NT>(Z, A.spec, A.ps, reinterpret_cast<double*>(tile));
+        return;
+      }
+    }
     zero_mode_part<NT>(Z, (int)blk, nzb);
     return;
   }
@@ -515,7 +548,7 @@ __device__ __forceinline__ void ytri_solve(const YArgs<T, U>& A, long q0, Cx<T>*
   {
     const int mm = threadIdx.x % M, row0 = threadIdx.x / M;
     const long qs = q0 + mm;
-    if (qs < Q && qs % A.rs < A.hp) {
+    if (qs < Q && qs % A.rs < A.hp && !(A.zcol && qs == 0)) {
 #pragma unroll
       for (int i = 0; i < K; ++i) {
         const int row = row0 + P * i;
