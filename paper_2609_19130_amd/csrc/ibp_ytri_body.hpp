@@ -228,7 +228,7 @@ __device__ __forceinline__ void zero_mode_column(const ZeroArgs& Z, Cx<double>* 
 // lane of a P-lane group inside one wave; the three recurrences are composed
 // per partition (eps by 2x2 Moebius matrices with non-negative entries, d'
 // and X by affine maps), chained across the
-// partitions with wave shuffles (Hillis-Steele), and each lane re-sweeps its
+// partitions with lane moves (scan_up, scan_down), and each lane re-sweeps its
 // K rows.  The block's M columns are staged through LDS so that global loads
 // and stores are M * element-size contiguous bytes per row.
 
@@ -266,10 +266,48 @@ __device__ __forceinline__ int exp2_of(float x) { return __builtin_amdgcn_frexp_
 __device__ __forceinline__ double scale2(double x, int k) { return __builtin_amdgcn_ldexp(x, k); }
 __device__ __forceinline__ float scale2(float x, int k) { return __builtin_amdgcn_ldexpf(x, k); }
 
-template <typename U>
-__device__ __forceinline__ U shfl_up_w(U v, int d, int w) { return __shfl_up(v, d, w); }
-template <typename U>
-__device__ __forceinline__ U shfl_down_w(U v, int d, int w) { return __shfl_down(v, d, w); }
+// Lane moves in the vector unit (DPP): CTRL row_shr / row_shl by 1..15 inside
+// rows of 16 lanes, wave_shr / wave_shl by 1, row_bcast 15 / 31 (lane 15 of a
+// row, lane 31, to the rows above).  Lanes without a source keep their value.
+template <int CTRL>
+__device__ __forceinline__ float lane_move(float v) {
+  const int x = __float_as_int(v);
+  return __int_as_float(__builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false));
+}
+template <int CTRL>
+__device__ __forceinline__ double lane_move(double v) {
+  const long long x = __double_as_longlong(v);
+  const int lo = (int)x, hi = (int)(x >> 32);
+  const unsigned l = (unsigned)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+  const unsigned h = (unsigned)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+  return __longlong_as_double((long long)(((unsigned long long)h << 32) | l));
+}
+constexpr int kRowShl = 0x100, kRowShr = 0x110, kWaveShl1 = 0x130, kWaveShr1 = 0x138, kRowBcast15 = 0x142,
+              kRowBcast31 = 0x143;
+
+// Inclusive scans over groups of P = 32 or 64 lanes: `step(from, on)` composes
+// a lane's map with the earlier (later) one that from(v) fetches, where `on`.
+// Rows of 16 lanes by doubling, then row totals: the moves stay in the vector
+// unit.  Line solve, LDS permutes -> here, us: 128 x 96 x 128 13.8 -> 11.8,
+// 384 x 256 x 320 98.8 -> 90.1; 512 x 384 x 512 368, bound by memory.
+template <int P, typename F>
+__device__ __forceinline__ void scan_up(int p, F&& step) {
+  step([](auto v) { return lane_move<kRowShr + 1>(v); }, (p & 15) >= 1);
+  step([](auto v) { return lane_move<kRowShr + 2>(v); }, (p & 15) >= 2);
+  step([](auto v) { return lane_move<kRowShr + 4>(v); }, (p & 15) >= 4);
+  step([](auto v) { return lane_move<kRowShr + 8>(v); }, (p & 15) >= 8);
+  step([](auto v) { return lane_move<kRowBcast15>(v); }, (p & 16) != 0);
+  if constexpr (P == 64) step([](auto v) { return lane_move<kRowBcast31>(v); }, (p & 32) != 0);
+}
+template <int P, typename F>
+__device__ __forceinline__ void scan_down(int p, F&& step) {
+  step([](auto v) { return lane_move<kRowShl + 1>(v); }, (p & 15) < 15);
+  step([](auto v) { return lane_move<kRowShl + 2>(v); }, (p & 15) < 14);
+  step([](auto v) { return lane_move<kRowShl + 4>(v); }, (p & 15) < 12);
+  step([](auto v) { return lane_move<kRowShl + 8>(v); }, (p & 15) < 8);
+  step([](auto v) { return __shfl(v, 16, 32); }, (p & 16) == 0);   // lane 16 of 32: the upper row's total
+  if constexpr (P == 64) step([](auto v) { return __shfl(v, 32, 64); }, (p & 32) == 0);
+}
 
 // Coalesced loads of the [ny][M] tile of columns q0 .. q0 + M - 1: thread
 // (row0 = tid / M, lm = tid % M) loads rows row0 + P*i, i < K, all issued
@@ -431,11 +469,10 @@ __device__ __forceinline__ void ytri_solve(const YArgs<T, U>& A, long q0, Cx<T>*
     mC = scale2(n10, ex);
     mD = scale2(n11, ex);
   }
-#pragma unroll
-  for (int off = 1; off < P; off <<= 1) {   // inclusive prefix: mine after the earlier ones
-    const U pA = shfl_up_w(mA, off, P), pB = shfl_up_w(mB, off, P);
-    const U pC = shfl_up_w(mC, off, P), pD = shfl_up_w(mD, off, P);
-    if (p >= off) {
+  // inclusive prefix: mine after the earlier ones
+  scan_up<P>(p, [&](auto from, bool on) {
+    const U pA = from(mA), pB = from(mB), pC = from(mC), pD = from(mD);
+    if (on) {
       const U n00 = mA * pA + mB * pC, n01 = mA * pB + mB * pD;
       const U n10 = mC * pA + mD * pC, n11 = mC * pB + mD * pD;
       const int ex = -exp2_of(n10 + n11);
@@ -444,12 +481,12 @@ __device__ __forceinline__ void ytri_solve(const YArgs<T, U>& A, long q0, Cx<T>*
       mC = scale2(n10, ex);
       mD = scale2(n11, ex);
     }
-  }
+  });
   {
     // eps entering the partition: the earlier composite applied to
     // eps_{-1} = 1 (the value beyond the lower wall does not depend on X_0)
-    const U eA = shfl_up_w(mA, 1, P), eB = shfl_up_w(mB, 1, P);
-    const U eC = shfl_up_w(mC, 1, P), eD = shfl_up_w(mD, 1, P);
+    const U eA = lane_move<kWaveShr1>(mA), eB = lane_move<kWaveShr1>(mB);
+    const U eC = lane_move<kWaveShr1>(mC), eD = lane_move<kWaveShr1>(mD);
     U e = (eA + eB) / (eC + eD);
     if (p == 0) e = U(1);
     // with the pivots known, keep a_j / D_j, c_j / D_j and F_j / D_j only
@@ -475,16 +512,14 @@ __device__ __forceinline__ void ytri_solve(const YArgs<T, U>& A, long q0, Cx<T>*
       mu = mi * mu;
       nu = csub(cscale(nu, mi), d[i]);
     }
-#pragma unroll
-    for (int off = 1; off < P; off <<= 1) {
-      const U pm = shfl_up_w(mu, off, P);
-      const U px = shfl_up_w(nu.x, off, P), py = shfl_up_w(nu.y, off, P);
-      if (p >= off) {
+    scan_up<P>(p, [&](auto from, bool on) {
+      const U pm = from(mu), px = from(nu.x), py = from(nu.y);
+      if (on) {
         nu = Cx<U>{mu * px + nu.x, mu * py + nu.y};
         mu = mu * pm;
       }
-    }
-    Cx<U> prev{shfl_up_w(nu.x, 1, P), shfl_up_w(nu.y, 1, P)};
+    });
+    Cx<U> prev{lane_move<kWaveShr1>(nu.x), lane_move<kWaveShr1>(nu.y)};
     if (p == 0) prev = Cx<U>{U(0), U(0)};
 #pragma unroll
     for (int i = 0; i < K; ++i) {
@@ -502,16 +537,15 @@ __device__ __forceinline__ void ytri_solve(const YArgs<T, U>& A, long q0, Cx<T>*
       Tt = tau * Tt;
       S = cadd(d[i], cscale(S, tau));
     }
-#pragma unroll
-    for (int off = 1; off < P; off <<= 1) {   // inclusive suffix: mine before the later ones
-      const U nT = shfl_down_w(Tt, off, P);
-      const U sx = shfl_down_w(S.x, off, P), sy = shfl_down_w(S.y, off, P);
-      if (p + off < P) {
+    // inclusive suffix: mine before the later ones
+    scan_down<P>(p, [&](auto from, bool on) {
+      const U nT = from(Tt), sx = from(S.x), sy = from(S.y);
+      if (on) {
         S = Cx<U>{Tt * sx + S.x, Tt * sy + S.y};
         Tt = Tt * nT;
       }
-    }
-    Cx<U> nxt{shfl_down_w(S.x, 1, P), shfl_down_w(S.y, 1, P)};
+    });
+    Cx<U> nxt{lane_move<kWaveShl1>(S.x), lane_move<kWaveShl1>(S.y)};
     if (p == P - 1) nxt = Cx<U>{U(0), U(0)};
 #pragma unroll
     for (int i = K - 1; i >= 0; --i) {
