@@ -41,24 +41,24 @@ void k_ycol(YArgs<double, double> A, ZeroArgs Z) {
   // the waves' composites: [wave][value][column]
   __shared__ double ex1[nw * 4 * M], ex2[nw * 3 * M], ex3[nw * 3 * M];
   const int nzb = zero_blocks(A);
-  long lb = blockIdx.x;
-  if (lb < nzb) {   // the first blocks: FP64 (0,0) mode
+  unsigned lb = blockIdx.x;
+  if (lb < (unsigned)nzb) {   // the first blocks: FP64 (0,0) mode
     if (A.zcol)
       zero_mode_column<nthreads>(Z, A.spec, A.ps, reinterpret_cast<double*>(tab));
     else
       zero_mode_part<nthreads>(Z, (int)lb, nzb);
     return;
   }
-  lb -= nzb;
+  lb -= (unsigned)nzb;
   const int ny = A.ny;
-  const long nkz = A.Q / A.rs;
+  const unsigned nkz = (unsigned)A.Q / (unsigned)A.rs;   // a plane has fewer than 2^31 columns
   // kx group by kx group, all kz of one before the next (the inverse z pass
   // starts on the groups written last); the two halves of a 128-byte line go
   // to blocks lb and lb + 8, which share an XCD
-  long grp = lb;
+  unsigned grp = lb;
   int h = 0;
   if constexpr (M == 4) {
-    const long nlb = A.Q / M, full = nlb / 16 * 16;
+    const unsigned nlb = (unsigned)A.Q / M, full = nlb / 16 * 16;
     if (lb < full) {
       grp = (lb / 16) * 8 + (lb % 8);
       h = (int)(lb % 16) / 8;

@@ -335,8 +335,40 @@ __device__ __forceinline__ void ytri_stage(int ny, int lm, int row0, const Cx<T>
   }
 }
 
+// A lane's column and its rows' face coefficients.  Up to 12 rows a lane they
+// are loaded after the field and before the staging barrier, so that their
+// latency (cold in every launch) passes with the field's; line solve, us:
+// 256 x 192 x 256 40.4 -> 35.8, 384 x 256 x 320 90 -> 81, 512 x 384 x 512
+// 368 -> 361.  At 16 rows that costs more than it hides (501 x 1001 x 501 913
+// -> 948): after the barrier there.
+template <typename U, int K>
+struct YCoef {
+  U a[K], c[K], L;
+  bool zero;
+};
+template <typename T, typename U, int M, int P, int K>
+__device__ __forceinline__ void ytri_coef(const YArgs<T, U>& A, long q0, YCoef<U, K>& C) {
+  const int p = threadIdx.x % P, m = threadIdx.x / P, s = p * K;
+  const unsigned q = (unsigned)q0 + m, rs = (unsigned)A.rs;   // Q < 2^31
+  const bool in = q < (unsigned)A.Q;
+  const int kz = in ? (int)(q / rs) : 0;
+  const int kx = in ? (int)(q - (unsigned)kz * rs) : 0;
+  const bool valid = in && kx < A.hp;   // row padding slots are not solved
+  const U lx = gbl(A.lamx)[valid ? kx : 0], lz = gbl(A.lamz)[kz];
+  // the tables are zero-padded to P*K rows, so rows past ny are decoupled
+  // (a = c = 0) and get shift 1
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    C.a[i] = gbl(A.ya)[s + i];
+    C.c[i] = gbl(A.yc)[s + i];
+  }
+  C.L = valid ? -(lx + lz) : U(1);
+  C.zero = A.singular && q == 0;
+  if (C.zero) C.L = U(1);   // singular (0,0): solved in FP64 by the (0,0)-mode blocks, zeroed here
+}
+
 template <typename T, typename U, int M, int P, int K, bool OUT64 = false, bool ADD = false>
-__device__ __forceinline__ void ytri_solve(const YArgs<T, U>& A, long q0, Cx<T>* tile,
+__device__ __forceinline__ void ytri_solve(const YArgs<T, U>& A, long q0, Cx<T>* tile, const YCoef<U, K>& C,
                                            const Cx<double> (*old)[K] = nullptr);
 
 // Block `blk` of one grid's line-solve pass: blocks [0, zero_blocks(ny))
@@ -363,9 +395,10 @@ __device__ __forceinline__ void ytri_body(const YArgs<T, U>& A, const ZeroArgs& 
     zero_mode_part<NT>(Z, (int)blk, nzb);
     return;
   }
-  long q0 = (blk - nzb) * M;
-  const long lb = blk - nzb, nkz = A.Q / A.rs;
-  if (kx_major && A.rs % M == 0) q0 = (lb % nkz) * A.rs + (lb / nkz) * M;
+  // 32-bit index arithmetic: a plane has fewer than 2^31 columns
+  const unsigned lb = (unsigned)(blk - nzb), nkz = (unsigned)A.Q / (unsigned)A.rs;
+  long q0 = (long)lb * M;
+  if (kx_major && A.rs % M == 0) q0 = (long)(lb % nkz) * A.rs + (long)(lb / nkz) * M;
   if constexpr (sizeof(Cx<T>) * M == 64) {
     // Half-line column groups (64 of a row's 128 bytes): the two groups of
     // one 128-byte line go to blocks lb and lb + 8, which the round-robin
@@ -375,8 +408,8 @@ __device__ __forceinline__ void ytri_body(const YArgs<T, U>& A, const ZeroArgs& 
     // remaining pairs two by two.  Rows of 128 bytes (rs a multiple of 2M)
     // give every group its sibling.
     if (A.rs % (2 * M) == 0) {
-      const long nlb = A.Q / M, full = nlb / 16 * 16;
-      long pair, h;
+      const unsigned nlb = (unsigned)A.Q / M, full = nlb / 16 * 16;
+      unsigned pair, h;
       if (lb < full) {
         pair = (lb / 16) * 8 + (lb % 8);
         h = (lb % 16) / 8;
@@ -384,12 +417,15 @@ __device__ __forceinline__ void ytri_body(const YArgs<T, U>& A, const ZeroArgs& 
         pair = full / 2 + (lb - full) / 2;
         h = (lb - full) % 2;
       }
-      q0 = kx_major ? (pair % nkz) * A.rs + (2 * (pair / nkz) + h) * M : (2 * pair + h) * M;
+      q0 = kx_major ? (long)(pair % nkz) * A.rs + (long)(2 * (pair / nkz) + h) * M : (long)(2 * pair + h) * M;
     }
   }
   const int lm = threadIdx.x % M, row0 = threadIdx.x / M;
   Cx<T> ld[K];
   ytri_load<T, U, M, P, K>(A, q0, lm, row0, ld);
+  constexpr bool kEarly = K <= 12;
+  YCoef<U, K> C;
+  if constexpr (kEarly) ytri_coef<T, U, M, P, K>(A, q0, C);
   if constexpr (ADD) {
     // the FP64 values the solution is added to, loaded with the input (the
     // store loop's rows and columns)
@@ -405,11 +441,13 @@ __device__ __forceinline__ void ytri_body(const YArgs<T, U>& A, const ZeroArgs& 
     }
     ytri_stage<T, M, P, K>(A.ny, lm, row0, ld, tile);
     __syncthreads();
-    ytri_solve<T, U, M, P, K, OUT64, true>(A, q0, tile, &old);
+    if constexpr (!kEarly) ytri_coef<T, U, M, P, K>(A, q0, C);
+    ytri_solve<T, U, M, P, K, OUT64, true>(A, q0, tile, C, &old);
   } else {
     ytri_stage<T, M, P, K>(A.ny, lm, row0, ld, tile);
     __syncthreads();
-    ytri_solve<T, U, M, P, K, OUT64>(A, q0, tile);
+    if constexpr (!kEarly) ytri_coef<T, U, M, P, K>(A, q0, C);
+    ytri_solve<T, U, M, P, K, OUT64>(A, q0, tile, C);
   }
 }
 
@@ -418,29 +456,22 @@ __device__ __forceinline__ void ytri_body(const YArgs<T, U>& A, const ZeroArgs& 
 // of an LDS buffer of ytile_slots FP64 entries, re-used as their FP64 staging
 // once every lane has read its staged rows.
 template <typename T, typename U, int M, int P, int K, bool OUT64, bool ADD>
-__device__ __forceinline__ void ytri_solve(const YArgs<T, U>& A, long q0, Cx<T>* tile,
+__device__ __forceinline__ void ytri_solve(const YArgs<T, U>& A, long q0, Cx<T>* tile, const YCoef<U, K>& C,
                                            const Cx<double> (*old)[K]) {
   constexpr int PS = K * M + 1;   // LDS slots per partition
   const int ny = A.ny;
   const long Q = A.Q;
   const int p = threadIdx.x % P, m = threadIdx.x / P;
-  const long q = q0 + m;
-  const int kz = q < Q ? (int)(q / A.rs) : 0;
-  const int kx = q < Q ? (int)(q - (long)kz * A.rs) : 0;
-  const bool valid = q < Q && kx < A.hp;   // row padding slots are not solved
-  U L = valid ? -(gbl(A.lamx)[kx] + gbl(A.lamz)[kz]) : U(1);
-  const bool zero = A.singular && q == 0;
-  if (zero) L = U(1);   // singular (0,0): solved in FP64 by the (0,0)-mode blocks, zeroed here
+  const U L = C.L;
+  const bool zero = C.zero;
   const int s = p * K;
   Cx<T>* my = tile + p * PS + m;   // row i of this lane's partition: my[i * M]
 
-  // face coefficients of this lane's rows: the tables are zero-padded to
-  // P*K rows, so rows past ny are decoupled (a = c = 0) and get shift 1
   U ca[K], cc[K];
 #pragma unroll
   for (int i = 0; i < K; ++i) {
-    ca[i] = gbl(A.ya)[s + i];
-    cc[i] = gbl(A.yc)[s + i];
+    ca[i] = C.a[i];
+    cc[i] = C.c[i];
   }
   Cx<U> d[K];
 #pragma unroll
@@ -582,7 +613,7 @@ __device__ __forceinline__ void ytri_solve(const YArgs<T, U>& A, long q0, Cx<T>*
   {
     const int mm = threadIdx.x % M, row0 = threadIdx.x / M;
     const long qs = q0 + mm;
-    if (qs < Q && qs % A.rs < A.hp && !(A.zcol && qs == 0)) {
+    if (qs < Q && (unsigned)qs % (unsigned)A.rs < (unsigned)A.hp && !(A.zcol && qs == 0)) {
 #pragma unroll
       for (int i = 0; i < K; ++i) {
         const int row = row0 + P * i;
