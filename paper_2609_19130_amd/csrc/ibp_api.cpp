@@ -203,7 +203,8 @@ bool z_small(const FftPlan& fpz, int nz) {
 // solve: not after Bluestein transforms, whose error in it is relative to the
 // whole line and not to its sum (the row sums stay the direct ones there).
 bool zero_from_column(const ibp_plan_s* p, bool xdirect, bool zdirect) {
-  return p->singular() && (xdirect || !p->fpx.blu) && (p->nz == 1 || zdirect || !p->fpz.blu);
+  return p->singular() && (xdirect || !(p->fpx.blu || p->xbm)) &&
+         (p->nz == 1 || zdirect || !(p->fpz.blu || p->zbm));
 }
 
 mdft::Plan mdft_plan(const MdftShape& m) { return mdft::Plan{m.S, m.P, m.MT, m.KT}; }
@@ -1547,6 +1548,8 @@ ibp_status_t enqueue_solve(ibp_plan_s* p, const double* rhs, double* phi, hipStr
   // FP64 direct solve: x R2C, z FFT, y line solves + FP64 (0,0), z inverse, x C2R
   XArgs<double> xa = xargs<double>(p, rhs, nullptr, phi, p->spec64, p->twx, p->rb64, 0);
   xa.parts = 0;   // no norms needed: non-finite input shows up in the FP64 plane sums
+  const bool zcol = zero_from_column(p, p->xfast || p->mx.S, p->zfast || p->mz.S);
+  if (zcol) xa.rowsum = nullptr;
   int xmode = XM_PLAIN;
   if (from_u) {
     xmode = XM_DIV;
@@ -1566,7 +1569,7 @@ ibp_status_t enqueue_solve(ibp_plan_s* p, const double* rhs, double* phi, hipStr
   YArgs<double, double> ya{p->spec64, p->lamx, p->lamz, p->ya, p->yc, p->ctl,
                            (long)p->nz * spec_row_stride<double>(p->hp), spec_row_stride<double>(p->hp),
                            spec_plane_stride<double>(p->hp, p->nz), p->ny, p->hp, 0, p->singular()};
-  ya.zcol = zero_from_column(p, p->xfast || p->mx.S, p->zfast || p->mz.S);
+  ya.zcol = zcol;
   IBP_LAUNCH(P_Y, launch_ytri<double, double>(p->yP, p->yK, p->ycols, ya, zargs(p, 0, 1, 0, 0, 0), s));
   return inverse_zx<double>(p, xa, CM_SET, P_XC2R, za, s);
 }
@@ -2103,6 +2106,7 @@ ibp_status_t batch_build(ibp_batch_s* b) {
         b->mlds[1] = std::max(b->mlds[1], mdft::lds_c2r(d.md.i.M, d.md.i.RS, d.md.i.RP));
       }
       d.y.zcol = zero_from_column(p, d.md.f.M.S != 0, d.md.z.M.S != 0);
+      if (d.y.zcol) d.x.rowsum = nullptr;
       if (d.md.z.M.S) b->mlds[2] = std::max(b->mlds[2], mdft::lds_z(d.md.z.M, d.md.z.RS));
     }
   }

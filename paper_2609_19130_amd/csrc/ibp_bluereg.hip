@@ -207,8 +207,8 @@ __global__ __launch_bounds__(blu_x_threads<M>()) void k_xblu_r2c(XArgs<T> A) {
   sa = row_total<TT>(sa, sh, lr);
   sb = row_total<TT>(sb, sh, lr);
   if (t == 0) {
-    if (live0) A.rowsum[r0] = sa;
-    if (live1) A.rowsum[r0 + 1] = sb;
+    if (live0 && A.rowsum != nullptr) A.rowsum[r0] = sa;
+    if (live1 && A.rowsum != nullptr) A.rowsum[r0 + 1] = sb;
   }
   Cx<T>* L = lds + lr * SS;
   blu_convolve<M, T, SH>(v, t, L, A.bb, A.bt);

@@ -88,10 +88,13 @@ __device__ __forceinline__ void xr2c_body(const XArgs<T>& A, long blk, Cx<T>* ld
     }
     v[i] = Cx<T>{T(v0 * s), T(v1 * s)};
   }
-  // FP64 row sum over the TT threads of the row (aligned power-of-two lane group)
+  // FP64 row sum over the TT threads of the row (aligned power-of-two lane
+  // group), unless the (0,0) mode takes the spectrum's column
+  if (kParts || A.rowsum != nullptr) {
 #pragma unroll
-  for (int off = TT / 2; off > 0; off >>= 1) rs += __shfl_xor(rs, off, kWave);
-  if (live && t == 0) A.rowsum[row] = rs;
+    for (int off = TT / 2; off > 0; off >>= 1) rs += __shfl_xor(rs, off, kWave);
+    if (live && t == 0) A.rowsum[row] = rs;
+  }
   if (kParts && A.parts) acc.write<NT, kRes>(A.part, blk, sh);
   Cx<T>* my = lds + lr * SS;
   P::run(v, t, my, A.twx, 2);

@@ -497,7 +497,7 @@ __device__ __forceinline__ void xr2c_tiles(const XArgs<double>& A, const XExtra&
           const unsigned o = (unsigned)(S * q) * sizeof(Cx<double>);
           if (sa) put(out, oa + o, Cx<double>{acc.cr[i], acc.sr[i]});
           if (sb) put(out, ob + o, Cx<double>{acc.ci[i], acc.si[i]});
-          if (q == 0) {   // the row sums
+          if (q == 0 && A.rowsum != nullptr) {   // the row sums
             if (sa) A.rowsum[row0 + 2 * col] = acc.cr[i];
             if (sb) A.rowsum[row0 + 2 * col + 1] = acc.ci[i];
           }

@@ -126,7 +126,7 @@ __device__ __forceinline__ void xr2c_gen_body(const XArgs<T>& A, const FftPlan& 
       if (MODE != XM_RESID_ONLY) buf[lr * hs + m] = Cx<T>{T(v0 * s), T(v1 * s)};
     }
     rs = wave_sum(rs);
-    if (MODE != XM_RESID_ONLY && lane == 0) gbl(A.rowsum)[row] = rs;
+    if (MODE != XM_RESID_ONLY && lane == 0 && A.rowsum != nullptr) gbl(A.rowsum)[row] = rs;
   }
   if (kParts && A.parts) acc.write<kThreads, kRes>(gbl(A.part), blk, sh);
   if (MODE == XM_RESID_ONLY) return;
