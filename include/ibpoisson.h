@@ -192,10 +192,10 @@ ibp_status_t ibp_solve_scratch(ibp_plan_t plan, const double* rhs, double* phi, 
  * workspace changed) allocates and synchronises; later calls do neither.
  * Callers that capture graphs from the first call build the batch
  * explicitly with ibp_batch_create.  Otherwise the plans are solved one after
- * another on `stream`.  The batched stages use the general mixed-radix
- * transforms for every grid, so results can differ from ibp_solve's in the
- * last bits for grids that ibp_solve transforms with its power-of-two
- * kernels. */
+ * another on `stream`.  The batched stages transform every grid with
+ * matrix products (FP64, lengths S P with S <= 8) or the general mixed-radix
+ * kernels, so results can differ from ibp_solve's in the last bits, e.g. for
+ * grids that ibp_solve transforms with its power-of-two kernels. */
 ibp_status_t ibp_solve_batched(const ibp_plan_t* plans, int count, const double* const* rhs,
                                double* const* phi, hipStream_t stream);
 
