@@ -889,6 +889,10 @@ ibp_status_t ibp_plan_set_precision(ibp_plan_t p, ibp_precision_t prec, double r
   p->prec = prec;
   ++p->gen;
   try {
+    if (prec != IBP_FP64 && p->xsmall != x_small(p->fpx, p->h)) {   // an x tile tuned for FP64
+      p->xsmall = x_small(p->fpx, p->h);
+      set_x_split(p);
+    }
     apply_cached_plan(p);
   } catch (...) {
     return IBP_ERROR_INTERNAL;
@@ -2461,9 +2465,10 @@ void tune_cache_put(const std::string& key, const TuneCfg& c, double ms) {
   tune_file_put(path, key, c, ms);
 }
 
-// Plans: whether the general x / z transforms may take either LDS tile.
+// Plans: whether the general x / z transforms may take either LDS tile (x:
+// FP64 only, the mixed forms' norm partials follow the x split).
 bool plan_x_tile_choice(const ibp_plan_s* p) {
-  return !p->xfast && x_small(p->fpx, p->h) && p->chunk == 0 && !p->fused;
+  return p->prec == IBP_FP64 && !p->xfast && x_small(p->fpx, p->h) && p->chunk == 0 && !p->fused;
 }
 bool plan_z_tile_choice(const ibp_plan_s* p) { return !p->zfast && p->nz > 1 && z_small(p->fpz, p->nz); }
 

@@ -602,12 +602,14 @@ template <typename T>
 hipError_t launch_xc2r(int mode, bool small, bool wide, const XArgs<T>& a, hipStream_t s);
 template <typename T>
 hipError_t launch_zfft(bool inverse, bool small, bool wide, const ZfArgs<T>& a, int nplanes, hipStream_t s);
-// M columns per block: `want` (2, 4, 8 or 16) if given, else 128-byte rows;
-// capped by the LDS budget.
 // Line solves of an FP64 spectrum with the columns in registers (ycol_rows:
-// the row counts that launch_ytri hands to them unless columns are asked for).
+// the row counts that launch_ytri hands to them).
 bool ycol_rows(int ny);
 hipError_t launch_ycol(const YArgs<double, double>& a, const ZeroArgs& z, hipStream_t s);
+// M columns per block: `want` (2, 4, 8 or 16) if given, else 128-byte rows;
+// capped by the LDS budget.  FP64 row counts of ycol_rows take launch_ycol
+// whatever `want` is: the two kernels associate their scans differently, and
+// `want` is a tuned choice, which must not change a bit.
 template <typename T, typename U>
 hipError_t launch_ytri(int P, int K, int want, const YArgs<T, U>& a, const ZeroArgs& z, hipStream_t s);
 // FP32 half spectrum in, FP64 arithmetic, FP64 half spectrum a.out64 out.

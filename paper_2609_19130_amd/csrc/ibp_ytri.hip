@@ -133,7 +133,7 @@ constexpr bool ytri_pair_used(int P, int K) { return P == 32 ? K <= 12 : K >= 8;
 
 
 static int ycol_override() {
-  const char* e = getenv("IBP_YCOLS");   // tuning knob: columns per line-solve block
+  const char* e = getenv("IBP_YCOLS");   // comparison runs: the staged kernel, columns per block
   return e ? atoi(e) : 0;
 }
 
@@ -177,7 +177,7 @@ static hipError_t launch_ytri_mp(int K, const YArgs<T, U>& a, const ZeroArgs& z,
 template <typename T, typename U>
 hipError_t launch_ytri(int P, int K, int want, const YArgs<T, U>& a, const ZeroArgs& z, hipStream_t s) {
   if constexpr (sizeof(T) == 8)
-    if (!want && !ycol_override() && ycol_rows(a.ny)) return launch_ycol(a, z, s);
+    if (!ycol_override() && ycol_rows(a.ny)) return launch_ycol(a, z, s);
   const int M = ytri_cols<T>(P, K, want);
   if (P == 32) {
     switch (M) {
