@@ -267,13 +267,15 @@ typedef struct {
  *
  * Tuning cache: when the environment variable IBP_TUNE_CACHE names a file,
  * every tuned choice is appended to it as one JSON line keyed by the device
- * architecture, the grid dimensions and the precision form, e.g.
- *   {"key": "gfx950/plan/512x384x512/0", "xdiv": 1, "zdiv": 1, "ycols": 8,
+ * architecture, the revision of the kernels, the grid dimensions and the
+ * precision form, e.g.
+ *   {"key": "gfx950.2/plan/512x384x512/0", "xdiv": 1, "zdiv": 1, "ycols": 8,
  *    "xsmall": -1, "zsmall": -1, "persistent": 0, "lag": 1, "chunk": 8, "ms": 1.67}
- * (batches: "gfx950/batch/<precision>.<max_iters>/<nx>x<ny>x<nz>,..." over
+ * (batches: "gfx950.2/batch/<precision>.<max_iters>/<nx>x<ny>x<nz>,..." over
  * their grids in order).  A key found there is applied without a search
  * (tried = 0), and ibp_plan_create, ibp_plan_set_precision and
- * ibp_batch_create apply it by themselves.  The last line of a key wins. */
+ * ibp_batch_create apply it by themselves.  The last line of a key wins;
+ * lines of another revision (or of none) are not read. */
 ibp_status_t ibp_plan_autotune(ibp_plan_t plan, const double* rhs, double* phi, hipStream_t stream, ibp_tune_t* out);
 
 /* The same for a batch (x rows, z columns and line-solve columns per block

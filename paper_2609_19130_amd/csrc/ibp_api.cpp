@@ -2413,11 +2413,16 @@ namespace {
 
 // ---- tuning cache
 // A text file of JSON lines, one per tuned configuration:
-//   {"key": "<arch>/plan/<nx>x<ny>x<nz>/<precision>", "xdiv": 1, "zdiv": 1, "ycols": 4,
+//   {"key": "<arch>.<rev>/plan/<nx>x<ny>x<nz>/<precision>", "xdiv": 1, "zdiv": 1, "ycols": 4,
 //    "xsmall": 1, "zsmall": 1, "persistent": 0, "lag": 1, "chunk": 8, "ms": 1.23}
-// Batch keys are "<arch>/batch/<precision>.<max_iters>/<nx>x<ny>x<nz>,..." over
-// the batch's grids in order.  The last line of a key wins.  <arch> is the
-// device's gfx architecture name (e.g. gfx950).
+// Batch keys are "<arch>.<rev>/batch/<precision>.<max_iters>/<nx>x<ny>x<nz>,..."
+// over the batch's grids in order.  The last line of a key wins.  <arch> is the
+// device's gfx architecture name (e.g. gfx950), <rev> kTuneRev: raised when the
+// kernels that a choice selects between change, so that choices timed on the
+// former ones no longer match (lines without it: the kernels before the
+// matrix products, whose z column choice costs those a third: 2.4 against
+// 1.8 ms a pass at 632 x 1263 x 632).
+constexpr int kTuneRev = 2;
 std::mutex g_tune_mu;
 
 std::string tune_cache_path() {
@@ -2435,12 +2440,14 @@ std::string device_arch(int device) {
 
 std::string plan_key(const ibp_plan_s* p) {
   char buf[160];
-  snprintf(buf, sizeof buf, "%s/plan/%dx%dx%d/%d", device_arch(p->device).c_str(), p->nx, p->ny, p->nz, (int)p->prec);
+  snprintf(buf, sizeof buf, "%s.%d/plan/%dx%dx%d/%d", device_arch(p->device).c_str(), kTuneRev, p->nx, p->ny, p->nz,
+           (int)p->prec);
   return buf;
 }
 
 std::string batch_key(const ibp_batch_s* b) {
-  std::string k = device_arch(b->device) + "/batch/" + std::to_string((int)b->prec) + "." +
+  std::string k = device_arch(b->device) + "." + std::to_string(kTuneRev) + "/batch/" +
+                  std::to_string((int)b->prec) + "." +
                   std::to_string(b->prec == IBP_FP64 ? 0 : b->max_iters) + "/";
   for (int g = 0; g < b->count; ++g) {
     const ibp_plan_s* p = b->plans[g];
@@ -2568,8 +2575,7 @@ ibp_status_t ibp_plan_autotune(ibp_plan_t p, const double* rhs, double* phi, hip
   try {
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool can_x = plan_x_tile_choice(p), can_z = plan_z_tile_choice(p);
-    const int zd0 = p->zc64max / (p->zc64 > 0 ? p->zc64 : 1);
-    const TuneCfg now{1, zd0 > 0 ? zd0 : 1, p->ycols, 0, 1, 8, p->xsmall ? 1 : 0, p->zsmall ? 1 : 0};
+    const TuneCfg now{1, p->zdiv, p->ycols, 0, 1, 8, p->xsmall ? 1 : 0, p->zsmall ? 1 : 0};
     auto apply = [&](const TuneCfg& c) {
       apply_plan_cfg(p, c);
       return IBP_SUCCESS;
@@ -2579,14 +2585,22 @@ ibp_status_t ibp_plan_autotune(ibp_plan_t p, const double* rhs, double* phi, hip
     TuneCfg cached;
     if (tune_cache_get(key, &cached)) return autotune({cached}, apply, run, s, out, true);
     std::vector<TuneCfg> cands{now};   // the configuration in place first
-    const bool zgen = !p->zfast && p->nz > 1;
+    // only what changes a launch: FP64 products have two z tiles (zdiv 1, and 2
+    // or more) and no LDS tiles, and the register line solve has one shape
+    const bool f64 = p->prec == IBP_FP64;
+    const int zmost = p->zfast || p->nz == 1 ? 1 : (f64 && p->mz.S ? 2 : 4);
+    const bool yone = f64 && ycol_rows(p->ny);
     for (int xs : {1, 0}) {
-      if (!can_x && xs != now.xsmall) continue;
+      if (!(can_x && !p->mx.S) && xs != now.xsmall) continue;
       for (int zs : {1, 0}) {
-        if (!can_z && zs != now.zsmall) continue;
-        for (int zd : {1, 2, 4}) {
-          if (!zgen && zd > 1) continue;
-          for (int yc : {2, 4, 8, 16}) cands.push_back(TuneCfg{1, zd, yc, 0, 1, 8, xs, zs});
+        if (!(can_z && !(f64 && p->mz.S)) && zs != now.zsmall) continue;
+        for (int zd = 1; zd <= zmost; zd *= 2) {
+          for (int yc : {2, 4, 8, 16}) {
+            if (yone && yc != 2) continue;
+            const TuneCfg c{1, zd, yone ? 0 : yc, 0, 1, 8, xs, zs};
+            if (yone && c.zdiv == now.zdiv && xs == now.xsmall && zs == now.zsmall) continue;   // the one in place
+            cands.push_back(c);
+          }
         }
       }
     }

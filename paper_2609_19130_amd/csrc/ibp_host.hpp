@@ -77,9 +77,9 @@ LineLu line_lu(std::vector<double> lo, std::vector<double> di, std::vector<doubl
 
 // ---------------------------------------------------------------- tuning cache
 // A text file of JSON lines, one per tuned configuration:
-//   {"key": "<arch>/plan/<nx>x<ny>x<nz>/<precision>", "xdiv": 1, "zdiv": 1, "ycols": 4,
+//   {"key": "<arch>.<rev>/plan/<nx>x<ny>x<nz>/<precision>", "xdiv": 1, "zdiv": 1, "ycols": 4,
 //    "xsmall": 1, "zsmall": 1, "persistent": 0, "lag": 1, "chunk": 8, "ms": 1.23}
-// Batch keys are "<arch>/batch/<precision>.<max_iters>/<nx>x<ny>x<nz>,..." over
+// Batch keys are "<arch>.<rev>/batch/<precision>.<max_iters>/<nx>x<ny>x<nz>,..." over
 // the batch's grids in order.  The last valid line of a key wins; a line
 // with a field outside its range is skipped.
 struct TuneCfg {

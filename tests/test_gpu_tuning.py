@@ -70,3 +70,33 @@ def test_choice_tuned_for_fp64_does_not_follow_into_a_mixed_form(monkeypatch, tm
     p.set_precision("mixed", max_iters=3)
     assert torch.equal(p.solve(f), ref)
     p.close()
+
+
+def test_lines_of_other_kernels_are_not_applied(monkeypatch, tmp_path):
+    """A cache line timed before the kernels it chooses between changed (no
+    revision in its key) leaves a plan to its defaults and to a new search."""
+    nx, ny, nz = 96, 40, 80
+    cache = tmp_path / "tune.jsonl"
+    old = {"key": f"gfx950/plan/{nx}x{ny}x{nz}/0", "xdiv": 1, "zdiv": 4, "ycols": 2, "xsmall": 0, "zsmall": 0,
+           "persistent": 0, "lag": 1, "chunk": 8, "ms": 0.1}
+    cache.write_text(json.dumps(old) + "\n")
+    monkeypatch.setenv("IBP_TUNE_CACHE", str(cache))
+    f = to_dev(np.random.default_rng(4).standard_normal((ny, nz, nx)))
+    p = plan_of(nx, ny, nz, "fp64")
+    assert p.autotune(f)["tried"] > 0
+    again = plan_of(nx, ny, nz, "fp64")
+    assert again.autotune(f)["tried"] == 0
+    for q in (p, again):
+        q.close()
+
+
+@pytest.mark.parametrize("nx,ny,nz,most", [(32, 600, 32, 1), (96, 600, 80, 2), (96, 40, 80, 9)])
+def test_only_configurations_that_differ_are_timed(monkeypatch, nx, ny, nz, most):
+    """FP64: register transforms with the register line solve have one
+    configuration, products two z tiles, the staged line solve four column
+    counts."""
+    monkeypatch.delenv("IBP_TUNE_CACHE", raising=False)
+    f = to_dev(np.random.default_rng(5).standard_normal((ny, nz, nx)))
+    p = plan_of(nx, ny, nz, "fp64")
+    assert 1 <= p.autotune(f)["tried"] <= most
+    p.close()
