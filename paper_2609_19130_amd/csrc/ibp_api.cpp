@@ -59,7 +59,8 @@ struct ibp_plan_s {
   // FP64 matrix-product transforms (S = 0: off) and their tiles
   // (set_mdft_split)
   MdftShape mx, mz;
-  mdft::XExtra mxf{}, mxi{};   // R2C, C2R
+  bool mxon = false, mxdon = false, mzon = false;   // passes that take them: x, assembled x R2C, z (choose_mdft)
+  mdft::XExtra mxf{}, mxi{}, mxd{};   // R2C, C2R, R2C of an assembled right-hand side
   int mzlc = 0, mzRS = 0;
   int cus = 256;   // compute units of the device
   int zdiv = 1;
@@ -214,23 +215,39 @@ mdft::Plan mdft_plan(const MdftShape& m) { return mdft::Plan{m.S, m.P, m.MT, m.K
 // products are (384-point rows at 384 x 256 x 320: 10 pairs, two blocks of
 // four waves, 4.3 TB/s against 3.4 for 6 pairs, two blocks of three), but
 // few enough for a tile on every compute unit (`rows` of them in the grid).
+// Where that gives some compute unit more than `slack` times its share of the
+// rows, the largest tile that does not: one round of larger tiles or whole
+// rounds (us: R2C of 4096 rows of 1280 points 43.7 -> 36.5, C2R of 4096 rows
+// of 384 points 15.1 -> 13.4).  `least` pairs where the rows go round: one
+// pair a tile (assembled right-hand side) reads a third row of w for every
+// two, 32768 rows of 720 points 265 us against 194 for four; tiles of equal
+// score go to the larger there.
 template <typename Lds>
-int mdft_rows(int S, int points, int per, size_t lim, long rows, int cus, Lds lds) {
+int mdft_rows(int S, int points, int per, size_t lim, long rows, int cus, int cu, double slack, int least, Lds lds) {
   const int most = mdft::max_threads(S) * mdft::tasks_per_thread(S);
-  int best = 1;
+  const long many = 1L << 20;   // tiles per compute unit: no fewer blocks there than LDS admits
+  auto fits = [&](int r) {
+    return r * points <= most && lds(r * per | 1, r) <= lim &&
+           mdft::block_threads(S, r * points, 0, lds(r * per | 1, r), many, cu) <= mdft::max_threads(S);
+  };
+  auto busiest = [&](int r) { return ((rows + r - 1) / r + cus - 1) / cus * r; };
+  if (!fits(least) || rows < (long)least * cus) least = 1;
+  int best = least;
   double best_score = 0.0;
-  for (int r = 1; r == 1 || (r * points <= most && lds(r * per | 1, r) <= lim); ++r) {
+  for (int r = least; r == least || (fits(r) && rows >= (long)r * cus); ++r) {
     const size_t bytes = lds(r * per | 1, r);
-    const int nt = mdft::block_threads(S, r * points, bytes), cols = (r * per + 15) / 16 * 16;
-    if (nt > mdft::max_threads(S)) break;
-    if (r > 1 && rows < (long)r * cus) break;
-    const double score = (double)mdft::blocks_per_cu(S, nt, bytes) * r * (r * per) / cols;
-    if (score > best_score * 1.02) {
+    const int nt = mdft::block_threads(S, r * points, 0, bytes, many, cu), cols = (r * per + 15) / 16 * 16;
+    const double score = (double)mdft::blocks_per_cu(nt, bytes, cu) * r * (r * per) / cols;
+    if (score > best_score * (least > 1 ? 0.98 : 1.02)) {
       best = r;
       best_score = score;
     }
   }
-  return best;
+  if (busiest(best) <= slack * busiest(1)) return best;
+  int even = 1;
+  for (int r = 2; fits(r) && r <= slack * busiest(1); ++r)
+    if (busiest(r) <= slack * busiest(1)) even = r;
+  return even;
 }
 
 // LDS row stride of 2^lc columns: neighbouring rows C = 2^lc values apart in
@@ -250,11 +267,18 @@ void set_mdft_split(ibp_plan_s* p) {
     const mdft::Plan M = mdft_plan(p->mx);
     const size_t lim = mdft::kMaxLds;
     const long rows = (long)p->ny * p->nz;
-    p->mxf.M = p->mxi.M = M;
-    p->mxf.cus = p->mxi.cus = p->cus;
-    p->mxf.RP = mdft_rows(S, P, kh, lim, (rows + 1) / 2, p->cus, [&](int rs, int) { return mdft::lds_r2c(M, rs); });
+    p->mxf.M = p->mxi.M = p->mxd.M = M;
+    p->mxf.cus = p->mxi.cus = p->mxd.cus = p->cus;
+    auto pairs = [&](bool assembled) {
+      return mdft_rows(S, P, kh, lim, (rows + 1) / 2, p->cus, mdft::cu_threads(S, assembled), 1.2, assembled ? 2 : 1,
+                       [&](int rs, int) { return mdft::lds_r2c(M, rs); });
+    };
+    p->mxf.RP = pairs(false);
     p->mxf.RS = (p->mxf.RP * kh) | 1;
-    p->mxi.RP = mdft_rows(S, P / 2 + 1, S, lim, rows, p->cus, [&](int rs, int rp) { return mdft::lds_c2r(M, rs, rp); });
+    p->mxd.RP = pairs(true);
+    p->mxd.RS = (p->mxd.RP * kh) | 1;
+    p->mxi.RP = mdft_rows(S, P / 2 + 1, S, lim, rows, p->cus, mdft::max_threads(S), 1.1, 1,
+                          [&](int rs, int rp) { return mdft::lds_c2r(M, rs, rp); });
     p->mxi.RS = (p->mxi.RP * S) | 1;
   }
   if (p->mz.S) {
@@ -273,6 +297,15 @@ void set_mdft_split(ibp_plan_s* p) {
     p->mzlc = lc;
     p->mzRS = mdft_z_stride(S, lc);
   }
+}
+
+// The passes of a plan that take the products: where a shape exists (IBP_MDFT=0:
+// none, for comparison runs).
+void choose_mdft(ibp_plan_s* p) {
+  const char* e = getenv("IBP_MDFT");
+  if (e && atoi(e) == 0) p->mx = p->mz = MdftShape{};
+  p->mxon = p->mxdon = p->mx.S != 0;
+  p->mzon = p->mz.S != 0;
 }
 
 // The FP64 and FP32 half spectra are separate regions: the FP64 inverse
@@ -645,12 +678,8 @@ ibp_status_t ibp_plan_create(ibp_plan_t* out, int nx, int ny, int nz, double Lx,
     p->xbm = reg_bluestein_length(fpx, nx, 1024);
     p->zbm = nz > 1 ? reg_bluestein_length(fpz, nz, 1024) : 0;
     // FP64 lines without register power-of-two kernels: matrix products
-    // (IBP_MDFT=0 turns them off, for comparison runs)
-    const char* md = getenv("IBP_MDFT");
-    if (md == nullptr || atoi(md) != 0) {
-      if (!rfft::supported(p->h) && nx <= 2048) p->mx = mdft_shape(nx);
-      if (!rfft::supported(nz) && nz <= 1024) p->mz = mdft_shape(nz);
-    }
+    if (!rfft::supported(p->h) && nx <= 2048) p->mx = mdft_shape(nx);
+    if (!rfft::supported(nz) && nz <= 1024) p->mz = mdft_shape(nz);
     ytri_shape(ny, &p->yP, &p->yK);
     p->xfast = rfft::supported(p->h);
     p->zfast = rfft::supported(nz);
@@ -857,6 +886,7 @@ ibp_status_t ibp_plan_create(ibp_plan_t* out, int nx, int ny, int nz, double Lx,
       release(p);
       return from_hip(e);
     }
+    choose_mdft(p);
     apply_cached_plan(p);
     *out = p;
     return IBP_SUCCESS;
@@ -1383,7 +1413,9 @@ template <typename T>
 hipError_t run_xr2c(const ibp_plan_s* p, int mode, const XArgs<T>& a, hipStream_t s) {
   if (p->xfast && mode != XM_RESID_ONLY) return launch_xr2c_fast<T>(mode, a, s);
   if constexpr (sizeof(T) == 8)
-    if (p->mx.S && (mode == XM_PLAIN || mode == XM_DIV)) return mdft::launch_xr2c(mode, a, p->mxf, s);
+    if (mode == XM_PLAIN && p->mxon) return mdft::launch_xr2c(mode, a, p->mxf, s);
+  if constexpr (sizeof(T) == 8)
+    if (mode == XM_DIV && p->mxdon) return mdft::launch_xr2c(mode, a, p->mxd, s);
   // register Bluestein: the FP64 right-hand side pass (the others keep the
   // LDS kernels, whose norm partials and residual modes it does not carry)
   if constexpr (sizeof(T) == 8)
@@ -1405,7 +1437,7 @@ template <typename T>
 hipError_t run_xc2r(const ibp_plan_s* p, int mode, const XArgs<T>& a, hipStream_t s) {
   if (p->xfast) return launch_xc2r_fast<T>(mode, a, s);
   if constexpr (sizeof(T) == 8)
-    if (p->mx.S) return mdft::launch_xc2r(mode, a, p->mxi, s);
+    if (p->mxon) return mdft::launch_xc2r(mode, a, p->mxi, s);
   if (p->xbm && p->chunk <= 0) return launch_xblu_c2r<T>(mode, with_xblu(p, a), p->xbm, s);
   return launch_xc2r<T>(mode, p->xsmall, p->xwide, a, s);
 }
@@ -1414,7 +1446,7 @@ template <typename T>
 hipError_t run_zfft(const ibp_plan_s* p, bool inverse, const ZfArgs<T>& a, int nplanes, hipStream_t s) {
   if (p->zfast) return launch_zfft_fast<T>(inverse, a, nplanes, s);
   if constexpr (sizeof(T) == 8) {
-    if (p->mz.S) {
+    if (p->mzon) {
       const mdft::ZArgs z{a.spec, a.twz, a.ctl, mdft_plan(p->mz), a.nz, a.hp, p->mzlc,
                           p->mzRS, a.rs, a.ps, a.check_done, a.plane0, p->cus};
       return mdft::launch_z(inverse, z, nplanes, s);
@@ -1552,7 +1584,7 @@ ibp_status_t enqueue_solve(ibp_plan_s* p, const double* rhs, double* phi, hipStr
   // FP64 direct solve: x R2C, z FFT, y line solves + FP64 (0,0), z inverse, x C2R
   XArgs<double> xa = xargs<double>(p, rhs, nullptr, phi, p->spec64, p->twx, p->rb64, 0);
   xa.parts = 0;   // no norms needed: non-finite input shows up in the FP64 plane sums
-  const bool zcol = zero_from_column(p, p->xfast || p->mx.S, p->zfast || p->mz.S);
+  const bool zcol = zero_from_column(p, p->xfast || (from_u ? p->mxdon : p->mxon), p->zfast || p->mzon);
   if (zcol) xa.rowsum = nullptr;
   int xmode = XM_PLAIN;
   if (from_u) {
@@ -2588,12 +2620,12 @@ ibp_status_t ibp_plan_autotune(ibp_plan_t p, const double* rhs, double* phi, hip
     // only what changes a launch: FP64 products have two z tiles (zdiv 1, and 2
     // or more) and no LDS tiles, and the register line solve has one shape
     const bool f64 = p->prec == IBP_FP64;
-    const int zmost = p->zfast || p->nz == 1 ? 1 : (f64 && p->mz.S ? 2 : 4);
+    const int zmost = p->zfast || p->nz == 1 ? 1 : (f64 && p->mzon ? 2 : 4);
     const bool yone = f64 && ycol_rows(p->ny);
     for (int xs : {1, 0}) {
-      if (!(can_x && !p->mx.S) && xs != now.xsmall) continue;
+      if (!(can_x && !p->mxon) && xs != now.xsmall) continue;
       for (int zs : {1, 0}) {
-        if (!(can_z && !(f64 && p->mz.S)) && zs != now.zsmall) continue;
+        if (!(can_z && !(f64 && p->mzon)) && zs != now.zsmall) continue;
         for (int zd = 1; zd <= zmost; zd *= 2) {
           for (int yc : {2, 4, 8, 16}) {
             if (yone && yc != 2) continue;

@@ -354,11 +354,17 @@ size_t lds_z(const Plan& M, int RS);
 size_t lds_r2c(const Plan& M, int RS);
 size_t lds_c2r(const Plan& M, int RS, int RP);
 int tasks_per_thread(int S);
-int block_threads(int S, int tasks, size_t lds);
-int blocks_per_cu(int S, int threads, size_t lds);
+int block_threads(int S, int tasks, int items, size_t lds, long tiles_per_cu, int cu);
+int blocks_per_cu(int threads, size_t lds, int cu);
 // Threads a block may have: the registers of S-point tasks (tasks_per_thread(S)
 // a thread) leave 128 each at 1024 threads, 168 at 768 and 256 at 512.
 __host__ __device__ constexpr int max_threads(int S) { return S <= 2 ? 1024 : S <= 8 ? 768 : 512; }
+// Threads that a compute unit holds (`cu` above).  The R2C of an assembled
+// right-hand side keeps no tile in flight and takes fewer registers at some S
+// (at most 128 for 7 and 8, 168 for 9..12).
+constexpr int cu_threads(int S, bool assembled) {
+  return !assembled ? max_threads(S) : S == 7 || S == 8 ? 1024 : S >= 9 && S <= 12 ? 768 : max_threads(S);
+}
 hipError_t launch_z(bool inverse, const ZArgs& a, int nplanes, hipStream_t s);
 hipError_t launch_xr2c(int mode, const XArgs<double>& a, const XExtra& e, hipStream_t s);
 hipError_t launch_xc2r(int mode, const XArgs<double>& a, const XExtra& e, hipStream_t s);

@@ -260,9 +260,10 @@ __device__ __forceinline__ Acc products(const Plan& M, const Cx<double>* roots, 
 // A block of each transform takes tiles first, first + stride, ... below
 // total.  Thread t owns the S-point tasks t, t + nthreads, ... of a tile (at
 // most TPT<S> of them), and the next tile's loads are in flight while the
-// products of the current one run and its results are stored.  Nothing else
-// is loaded from memory inside the loop (loads return in order, so waiting
-// for a later one would wait for the next tile's).
+// products of the current one run and its results are stored (but for the
+// assembled right-hand side).  Nothing else is loaded from memory inside the
+// loop (loads return in order, so waiting for a later one would wait for the
+// next tile's).
 template <int S>
 constexpr int TPT = S <= 3 ? 4 : S == 4 ? 3 : S <= 6 ? 2 : 1;
 
@@ -395,6 +396,11 @@ __device__ __forceinline__ void xr2c_tiles(const XArgs<double>& A, const XExtra&
                                            unsigned stride, unsigned total, int nthreads, Cx<double>* lds) {
   constexpr int KH = S / 2, KF = (S - 1) / 2;   // k = 1 .. KF of both rows are separated; S even: k = S/2 is real
   constexpr int NT = TPT<S>;
+  // An assembled right-hand side is loaded where it is used: its values are
+  // computed on arrival, so a tile in flight hides nothing and costs registers
+  // (S = 2..6 spilled 28..160 bytes a lane, S = 16 took 239; R2C, us: 4096 rows
+  // of 100 points 19.7 -> 12.2, 65536 rows 70 -> 52).
+  constexpr bool kLate = MODE == XM_DIV;
   const int tid = threadIdx.x;
   const int P = M.P, RS = E.RS, RP = E.RP, NC = RP * (1 + 2 * KH), n = A.nx, nz = A.nz, H = P / 2;
   const int rows = A.ny * nz;
@@ -415,41 +421,43 @@ __device__ __forceinline__ void xr2c_tiles(const XArgs<double>& A, const XExtra&
   const int ntile = (NC + 15) / 16, items = M.MT * ntile;
   const long pgap = A.ps - (long)nz * A.rs;
   Cx<double> v[NT][S];
-  auto load = [&](unsigned b) {
+  // a task's rows of tile b; rows past the end read the last row (a last row
+  // without a partner is its own)
+  auto load_task = [&](int i, unsigned b) {
     const int row0 = (int)b * 2 * RP;
     const char* f = reinterpret_cast<const char*>(A.f + (size_t)row0 * n);
+    const int p = tp[i], j = tj[i], last = rows - 1 - row0;
+    const int la = 2 * p < last ? 2 * p : last, lb = 2 * p + 1 < last ? 2 * p + 1 : last;
+    if constexpr (MODE == XM_DIV) {
+      const int j0 = row0 / nz, k0 = row0 - j0 * nz;
+      const int ja = qquo(k0 + la, qnz), jb = qquo(k0 + lb, qnz);
 #pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      // every task loads: rows past the end read the last row (a last row
-      // without a partner is its own)
-      const int p = tp[i], j = tj[i], last = rows - 1 - row0;
-      const int la = 2 * p < last ? 2 * p : last, lb = 2 * p + 1 < last ? 2 * p + 1 : last;
-      if constexpr (MODE == XM_DIV) {
-        const int j0 = row0 / nz, k0 = row0 - j0 * nz;
-        const int ja = qquo(k0 + la, qnz), jb = qquo(k0 + lb, qnz);
+      for (int r = 0; r < S; ++r) {
+        v[i][r].x = assemble_one(A, row0 + la, j0 + ja, k0 + la - __mul24(ja, nz), j + P * r);
+        v[i][r].y = assemble_one(A, row0 + lb, j0 + jb, k0 + lb - __mul24(jb, nz), j + P * r);
+      }
+    } else {
+      const unsigned oa = (unsigned)(la * n + j) * sizeof(double), ob = (unsigned)(lb * n + j) * sizeof(double);
 #pragma unroll
-        for (int r = 0; r < S; ++r) {
-          v[i][r].x = assemble_one(A, row0 + la, j0 + ja, k0 + la - __mul24(ja, nz), j + P * r);
-          v[i][r].y = assemble_one(A, row0 + lb, j0 + jb, k0 + lb - __mul24(jb, nz), j + P * r);
-        }
-      } else {
-        const unsigned oa = (unsigned)(la * n + j) * sizeof(double), ob = (unsigned)(lb * n + j) * sizeof(double);
-#pragma unroll
-        for (int r = 0; r < S; ++r) {
-          v[i][r].x = at_d(f + (size_t)(P * r) * sizeof(double), oa);
-          v[i][r].y = at_d(f + (size_t)(P * r) * sizeof(double), ob);
-        }
+      for (int r = 0; r < S; ++r) {
+        v[i][r].x = at_d(f + (size_t)(P * r) * sizeof(double), oa);
+        v[i][r].y = at_d(f + (size_t)(P * r) * sizeof(double), ob);
       }
     }
   };
+  auto load = [&](unsigned b) {
+#pragma unroll
+    for (int i = 0; i < NT; ++i) load_task(i, b);
+  };
   unsigned b = first;
   int rot = 0;
-  if (b < total) load(b);
+  if (!kLate && b < total) load(b);
   for (; b < total; b += stride) {
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
       const int p = tp[i];
       if (p >= RP) continue;
+      if (kLate) load_task(i, b);
       Cx<double>* const z = v[i];
       Dft<S, false, double>::run(z);
       // per row: a[k] = A_k W^{j k}, b[k] = B_k W^{j k}
@@ -470,7 +478,7 @@ __device__ __forceinline__ void xr2c_tiles(const XArgs<double>& A, const XExtra&
       }
     }
     __syncthreads();
-    if (b + stride < total) load(b + stride);
+    if (!kLate && b + stride < total) load(b + stride);
     const int row0 = (int)b * 2 * RP;
     const int j0 = row0 / nz, k0 = row0 - j0 * nz;
     // byte offsets from the tile's first row (a tile's few thousand values and

@@ -107,3 +107,32 @@ def test_non_finite_input_is_flagged(monkeypatch):
     f[3, 17, 40] = np.nan
     _, info = solve(monkeypatch, True, f, synth.tanh_faces(ny, 2.0))
     assert info["nonfinite_input"] == 1
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(640, 3, 5), (1536, 2, 7), (1000, 9, 64), (320, 64, 64), (18, 40, 33), (31, 16, 64)])
+def test_few_tiles_per_compute_unit(monkeypatch, nx, ny, nz):
+    """Rows from below one to sixteen per compute unit: blocks of more waves
+    than their tasks need, tiles chosen for even rounds, ragged last ones."""
+    yf = synth.tanh_faces(ny, 2.0)
+    f = field(nx, ny, nz)
+    got, _ = solve(monkeypatch, True, f, yf)
+    ref, _ = oracle.solve(f, 2 * np.pi, 1.7, yf)
+    assert rel(got, ref) <= TOL64
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(320, 3, 7), (350, 4, 5), (348, 3, 5), (290, 3, 4), (240, 5, 4), (186, 3, 5),
+                                      (116, 5, 6), (62, 7, 8), (375, 3, 5), (377, 3, 4), (319, 3, 6), (261, 5, 4),
+                                      (203, 3, 5), (155, 5, 4), (87, 3, 6), (31, 5, 8), (96, 301, 80), (720, 40, 31)])
+def test_assembled_right_hand_side_of_every_length_class(monkeypatch, nx, ny, nz):
+    """Every S, row pairs across planes (odd nz), blocks that loop."""
+    monkeypatch.setenv("IBP_MDFT", "1")
+    yf = synth.tanh_faces(ny, 2.0)
+    u, v, w = synth.uniform_velocity(nx, ny, nz, seed=nx)
+    q = field(nx, ny, nz) if nx % 2 else None
+    rhs = divergence(u, v, w, geometry(nx, ny, nz, 2 * np.pi, 1.7, yf))
+    rhs = (rhs - q if q is not None else rhs) / 0.3
+    plan = ibp.Plan(nx, ny, nz, 2 * np.pi, 1.7, yf)
+    phi = plan.solve_divergence(to_dev(u), to_dev(v), to_dev(w), 0.3, q=to_dev(q) if q is not None else None)
+    ref, _ = oracle.solve(rhs, 2 * np.pi, 1.7, yf)
+    assert rel(phi.cpu().numpy(), ref) <= TOL64
+    plan.close()
