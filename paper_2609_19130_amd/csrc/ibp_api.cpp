@@ -208,8 +208,6 @@ bool zero_from_column(const ibp_plan_s* p, bool xdirect, bool zdirect) {
          (p->nz == 1 || zdirect || !(p->fpz.blu || p->zbm));
 }
 
-mdft::Plan mdft_plan(const MdftShape& m) { return mdft::Plan{m.S, m.P, m.MT, m.KT}; }
-
 // Rows (pairs) per tile, `points` tasks and `per` LDS columns each: as many as
 // possible in flight on a compute unit, weighted by how full the 16-column
 // products are (384-point rows at 384 x 256 x 320: 10 pairs, two blocks of
@@ -264,7 +262,7 @@ int mdft_z_stride(int S, int lc) {
 void set_mdft_split(ibp_plan_s* p) {
   if (p->mx.S) {
     const int S = p->mx.S, P = p->mx.P, kh = 1 + 2 * (S / 2);
-    const mdft::Plan M = mdft_plan(p->mx);
+    const MdftShape M = p->mx;
     const size_t lim = mdft::kMaxLds;
     const long rows = (long)p->ny * p->nz;
     p->mxf.M = p->mxi.M = p->mxd.M = M;
@@ -283,7 +281,7 @@ void set_mdft_split(ibp_plan_s* p) {
   }
   if (p->mz.S) {
     const int S = p->mz.S, P = p->mz.P;
-    const mdft::Plan M = mdft_plan(p->mz);
+    const MdftShape M = p->mz;
     auto fits = [&](int lc) {
       return mdft::lds_z(M, mdft_z_stride(S, lc)) <= mdft::kMaxLds && (P << lc) <= mdft::max_threads(S) * mdft::tasks_per_thread(S);
     };
@@ -1447,7 +1445,7 @@ hipError_t run_zfft(const ibp_plan_s* p, bool inverse, const ZfArgs<T>& a, int n
   if (p->zfast) return launch_zfft_fast<T>(inverse, a, nplanes, s);
   if constexpr (sizeof(T) == 8) {
     if (p->mzon) {
-      const mdft::ZArgs z{a.spec, a.twz, a.ctl, mdft_plan(p->mz), a.nz, a.hp, p->mzlc,
+      const mdft::ZArgs z{a.spec, a.twz, a.ctl, p->mz, a.nz, a.hp, p->mzlc,
                           p->mzRS, a.rs, a.ps, a.check_done, a.plane0, p->cus};
       return mdft::launch_z(inverse, z, nplanes, s);
     }
@@ -2024,7 +2022,7 @@ void batch_mdft(const ibp_plan_s* p, mdft::BatchPlan& md, const ZfArgs<double>& 
   const long nrows = (long)p->ny * p->nz;
   const MdftShape x = p->nx <= 2048 ? mdft_shape(p->nx) : MdftShape{};
   if (x.S && x.S <= 8) {
-    const mdft::Plan M = mdft_plan(x);
+    const MdftShape M = x;
     const int kh = 1 + 2 * (x.S / 2), most = kThreads * mdft::tasks_per_thread(x.S);
     // the most rows that a block's threads and LDS hold
     auto rows = [&](int points, auto lds) {
@@ -2043,7 +2041,7 @@ void batch_mdft(const ibp_plan_s* p, mdft::BatchPlan& md, const ZfArgs<double>& 
   }
   const MdftShape zs = p->nz > 1 && p->nz <= 1024 ? mdft_shape(p->nz) : MdftShape{};
   if (zs.S && zs.S <= 8) {
-    const mdft::Plan M = mdft_plan(zs);
+    const MdftShape M = zs;
     for (int lc : {4, 3}) {
       const int C = 1 << lc, RS = mdft_z_stride(zs.S, lc);
       if ((zs.P << lc) > kThreads * mdft::tasks_per_thread(zs.S) || mdft::lds_z(M, RS) > mdft::kBatchLds) continue;

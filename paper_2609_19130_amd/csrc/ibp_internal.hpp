@@ -308,12 +308,7 @@ hipError_t launch_x_roundtrip(const RtArgs& a, hipStream_t s);
 // Matrix-product transforms (ibp_mdft.hpp) of any length n = S P: FP64 z
 // lines and x rows.
 namespace mdft {
-// Plan of one length: MT 16-row and KT 4-deep steps (an even number) cover
-// P/2 + 1.
-struct Plan {
-  int S, P;
-  int MT, KT;
-};
+using Plan = MdftShape;
 
 struct ZArgs {
   Cx<double>* spec;
@@ -353,9 +348,10 @@ struct BatchPlan {
 size_t lds_z(const Plan& M, int RS);
 size_t lds_r2c(const Plan& M, int RS);
 size_t lds_c2r(const Plan& M, int RS, int RP);
-int tasks_per_thread(int S);
 int block_threads(int S, int tasks, int items, size_t lds, long tiles_per_cu, int cu);
 int blocks_per_cu(int threads, size_t lds, int cu);
+// S-point tasks a thread takes at most (they live in its registers).
+__host__ __device__ constexpr int tasks_per_thread(int S) { return S <= 3 ? 4 : S == 4 ? 3 : S <= 6 ? 2 : 1; }
 // Threads a block may have: the registers of S-point tasks (tasks_per_thread(S)
 // a thread) leave 128 each at 1024 threads, 168 at 768 and 256 at 512.
 __host__ __device__ constexpr int max_threads(int S) { return S <= 2 ? 1024 : S <= 8 ? 768 : 512; }

@@ -49,7 +49,6 @@ size_t lds_r2c(const Plan& M, int RS) { return lds_z(M, RS); }
 size_t lds_c2r(const Plan& M, int RS, int RP) {
   return ((size_t)(M.P / 2 + 2) * RS + M.P + (RP + 1) / 2) * sizeof(Cx<double>);
 }
-int tasks_per_thread(int S) { return S <= 3 ? 4 : S == 4 ? 3 : S <= 6 ? 2 : 1; }
 
 // Threads for `tasks` tasks and `items` 16-column products of a tile of `lds`
 // bytes: enough for the tasks, one a thread up to half the threads a block may

@@ -259,13 +259,11 @@ __device__ __forceinline__ Acc products(const Plan& M, const Cx<double>* roots, 
 
 // A block of each transform takes tiles first, first + stride, ... below
 // total.  Thread t owns the S-point tasks t, t + nthreads, ... of a tile (at
-// most TPT<S> of them), and the next tile's loads are in flight while the
-// products of the current one run and its results are stored (but for the
-// assembled right-hand side).  Nothing else is loaded from memory inside the
-// loop (loads return in order, so waiting for a later one would wait for the
-// next tile's).
-template <int S>
-constexpr int TPT = S <= 3 ? 4 : S == 4 ? 3 : S <= 6 ? 2 : 1;
+// most tasks_per_thread(S) of them), and the next tile's loads are in flight
+// while the products of the current one run and its results are stored (but
+// for the assembled right-hand side).  Nothing else is loaded from memory
+// inside the loop (loads return in order, so waiting for a later one would
+// wait for the next tile's).
 
 // ---------------------------------------------------------------- z lines
 // Column group and plane of a z tile.  Groups narrower than a 128-byte line
@@ -299,7 +297,7 @@ struct ZTiles {
 template <bool INV, int S, int LC>
 __device__ __forceinline__ void z_tiles(const ZArgs& A, const Plan& M, const ZTiles& Z, unsigned first,
                                         unsigned stride, unsigned total, int nthreads, Cx<double>* lds) {
-  constexpr int C = 1 << LC, NC = S << LC, ntile = (NC + 15) / 16, NT = TPT<S>;
+  constexpr int C = 1 << LC, NC = S << LC, ntile = (NC + 15) / 16, NT = tasks_per_thread(S);
   const int tid = threadIdx.x, P = M.P, RS = A.RS, H = P / 2;
   const unsigned rsb = (unsigned)A.rs * sizeof(Cx<double>);   // a plane's offsets stay below 2^32
   const int c = tid & (C - 1);   // nthreads is a multiple of C: every task of a thread has this column
@@ -395,7 +393,7 @@ template <int MODE, int S>
 __device__ __forceinline__ void xr2c_tiles(const XArgs<double>& A, const XExtra& E, const Plan& M, unsigned first,
                                            unsigned stride, unsigned total, int nthreads, Cx<double>* lds) {
   constexpr int KH = S / 2, KF = (S - 1) / 2;   // k = 1 .. KF of both rows are separated; S even: k = S/2 is real
-  constexpr int NT = TPT<S>;
+  constexpr int NT = tasks_per_thread(S);
   // An assembled right-hand side is loaded where it is used: its values are
   // computed on arrival, so a tile in flight hides nothing and costs registers
   // (S = 2..6 spilled 28..160 bytes a lane, S = 16 took 239; R2C, us: 4096 rows
@@ -544,7 +542,7 @@ template <int MODE, int S>
 __device__ __forceinline__ void xc2r_tiles(const XArgs<double>& A, const XExtra& E, const Plan& M, unsigned first,
                                            unsigned stride, unsigned base, unsigned total, unsigned end, int nthreads,
                                            Cx<double>* lds) {
-  constexpr int NT = TPT<S>;
+  constexpr int NT = tasks_per_thread(S);
   const int tid = threadIdx.x;
   const int P = M.P, RS = E.RS, RP = E.RP, NC = RP * S, n = A.nx, nz = A.nz;
   const int H = P / 2, NJ = H + 1;
