@@ -297,13 +297,19 @@ void set_mdft_split(ibp_plan_s* p) {
   }
 }
 
-// The passes of a plan that take the products: where a shape exists (IBP_MDFT=0:
-// none, for comparison runs).
+// The passes of a plan that take the products: where a shape exists and they
+// beat the kernels that the pass runs otherwise.  IBP_MDFT=0: none, 1: every
+// pass with a shape (comparison runs).
 void choose_mdft(ibp_plan_s* p) {
   const char* e = getenv("IBP_MDFT");
   if (e && atoi(e) == 0) p->mx = p->mz = MdftShape{};
-  p->mxon = p->mxdon = p->mx.S != 0;
-  p->mzon = p->mz.S != 0;
+  const bool all = e != nullptr;
+  const double rows = (double)p->ny * p->nz / p->cus, groups = (double)p->ny * ((p->hp + 7) / 8) / p->cus;
+  const int xblu = p->chunk <= 0 ? p->xbm : 0;
+  const bool xsums = p->fpx.any || p->fpx.blu;   // direct sums or Bluestein in the general kernels
+  p->mxon = p->mx.S && (all || (xblu == 0 && xsums) || mdft_x_pays(p->nx, p->mx, xblu, rows));
+  p->mxdon = p->mx.S && (all || mdft_div_pays(p->nx, xsums, rows));
+  p->mzon = p->mz.S && (all || mdft_z_pays(p->nz, p->mz, p->zbm, groups));
 }
 
 // The FP64 and FP32 half spectra are separate regions: the FP64 inverse

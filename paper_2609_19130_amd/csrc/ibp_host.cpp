@@ -159,6 +159,67 @@ MdftShape mdft_shape(int n) {
   return best;
 }
 
+// Measured on lengths of every S and on P up to 256, times of the other kernel
+// over the products' (above 1: products), x passes R2C and C2R together:
+//   register Bluestein, by points P of the products and rows per CU
+//     n <= 256       P 131: 0.77 (4)  1.06 (16)  1.14 (64)  1.60 (256)
+//                    P 149: 0.67      0.98       1.03       1.43
+//                    P 251: 0.48      0.73       0.85       1.00
+//     257..512       P 131: 0.78      1.17       1.33       1.54
+//                    P 181: 0.63      1.02       1.05       1.20
+//                    P 211: 0.57      0.77       0.67       0.94
+//     513..1024      P 131: 0.99      1.55       1.93       2.02
+//                    P 251 (753): 0.71 1.05 1.06 1.31, (1004): 0.77 0.72 0.94 1.04
+//   P <= 128: 1.0..2.4, but 0.9 to 64 rows per CU for 2 x 113 and 2 x 127.
+//   general kernels: 1.0..3.0 but for rows above 1152 points with one row per
+//   CU (1280: 0.93, 1536: 0.89).
+bool mdft_x_pays(int n, const MdftShape& m, int blu, double rows) {
+  if (blu == 0) return n <= 1152 || rows >= 2.0;
+  if (m.P <= 128) return blu != 512 || m.S != 2 || m.P <= 110 || rows >= 256.0;
+  if (blu <= 512) return rows >= (m.P <= 140 ? 16.0 : m.P <= 160 ? 64.0 : 256.0);
+  if (blu <= 1024) return m.P <= 192 && rows >= (m.P <= 160 ? 16.0 : 64.0);
+  return rows >= ((long)n * m.P <= 190000 ? 16.0 : 256.0);
+}
+
+// Seven loads a value: against the general kernel's pairs of values a load the
+// products win where that one runs direct sums (2 to 5), on short rows (up to
+// 200 points: 0.92..4.9), on odd lengths (375 points: 1.16..1.76) and where its
+// rows leave a tenth of its tile empty or more (1.0..1.3 from 32 rows per CU;
+// 0.8..0.95 on the others of 201..660 points, such as 320, 500 and 640).  Few
+// rows: 0.6..0.95 (4 per CU), 0.8..1.0 up to 520 points and 1.0..1.7 above (16).
+bool mdft_div_pays(int n, bool direct, double rows) {
+  if (direct || n <= 200) return true;
+  if (rows < 8.0) return false;
+  if (n % 2) return true;
+  if (rows < 32.0) return n > 520;
+  const int h = n / 2;
+  return n > 660 || 10 * (kTileX64s / h * h) < 9 * kTileX64s;
+}
+
+// As for x, one z pass, by column groups per CU:
+//   n <= 256       P 131: 0.75 (0.3)  0.86 (0.5)  0.85 (2.5)  1.00 (8)  1.17 (42)
+//                  P 191: 0.65        0.77        0.73        0.80      1.08
+//   257..512  S 2  P 131: 0.94        1.18        1.34        1.61      1.85
+//                  P 211: 0.72        0.87        0.76        0.81      0.90
+//             S 3  P 131: 0.64        0.81        0.94        1.26      1.53
+//                  P 167: 0.51        0.67        0.74        0.97      1.17
+//   513..1024 S 4  P 131: 1.14        1.51        1.69        2.03      2.30
+//                  P 227: 0.72        0.95        0.92        1.21
+//             S 3  P 191: 0.67        0.93        1.24        1.70      2.04
+//   P <= 128: above 0.95 but for S = 3 and 5 on a fraction of a group (0.8, 0.9).
+bool mdft_z_pays(int n, const MdftShape& m, int blu, double groups) {
+  if (blu == 0) return n <= 512 || groups >= 0.25;
+  if (m.P <= 128) return groups >= (blu < 1024 ? 0.0 : m.S == 3 ? 0.5 : m.S == 5 ? 0.25 : 0.0);
+  if (blu <= 512) return m.P <= 192 && groups >= (m.P <= 140 ? 8.0 : 32.0);
+  if (blu <= 1024) {
+    if (m.S == 2) return m.P <= 200 && groups >= (m.P <= 192 ? 0.5 : 32.0);
+    return groups >= (m.P <= 160 ? 8.0 : 32.0);
+  }
+  if (m.S == 3 && m.P <= 192) return groups >= 1.0;
+  if ((m.S == 5 && m.P > 192) || (long)n * m.P > 240000) return groups >= 32.0;
+  return groups >= (m.S >= 4 && (long)n * m.P <= 150000 ? 0.5 : 8.0);
+}
+
 // ---------------------------------------------------------------- line-solve shape
 // P = 32 lanes per column (P = 64 when ny > 384), K rows per lane from
 // {2, 4, 8, 12, 16, 24}.

@@ -56,6 +56,15 @@ struct MdftShape {
 // when every divisor S leaves P above kMdftMaxP.
 constexpr int kMdftMaxP = 256;
 MdftShape mdft_shape(int n);
+// Whether the products of shape m beat the kernels that take the length
+// otherwise.  blu: the register Bluestein's length for it, 0 where the general
+// kernels are the alternative; rows, groups: x rows and 128-byte column groups
+// (of all planes) per compute unit.  div: the assembled right-hand side, whose
+// alternative is always the general kernel; direct: its length has direct-sum
+// or Bluestein stages there.
+bool mdft_x_pays(int n, const MdftShape& m, int blu, double rows);
+bool mdft_div_pays(int n, bool direct, double rows);
+bool mdft_z_pays(int n, const MdftShape& m, int blu, double groups);
 // Dimension check: kDimsOk, kDimsInvalid (a size below 1) or
 // kDimsUnsupported (outside what the kernels cover).  On success fills the
 // x (half length) and z factorisations when the pointers are non-null.

@@ -136,3 +136,24 @@ def test_assembled_right_hand_side_of_every_length_class(monkeypatch, nx, ny, nz
     ref, _ = oracle.solve(rhs, 2 * np.pi, 1.7, yf)
     assert rel(phi.cpu().numpy(), ref) <= TOL64
     plan.close()
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(251, 3, 64), (502, 4, 251), (64, 5, 501), (1536, 2, 7), (334, 40, 64)])
+def test_lengths_that_choose_their_kernels_by_size(monkeypatch, nx, ny, nz):
+    """Without a request the solve and the solve of an assembled right-hand
+    side choose their kernels on their own (products, register Bluestein,
+    general), and with them where the (0,0) mode's sums come from."""
+    monkeypatch.delenv("IBP_MDFT", raising=False)
+    yf = synth.tanh_faces(ny, 2.0)
+    u, v, w = synth.uniform_velocity(nx, ny, nz, seed=7)
+    rhs = divergence(u, v, w, geometry(nx, ny, nz, 2 * np.pi, 1.7, yf)) / 0.3
+    for bc in (("neumann", "neumann"), ("neumann", "dirichlet")):
+        plan = ibp.Plan(nx, ny, nz, 2 * np.pi, 1.7, yf, bc=bc)
+        f = field(nx, ny, nz)
+        ref, m = oracle.solve(f, 2 * np.pi, 1.7, yf, bc=bc)
+        assert rel(plan.solve(to_dev(f)).cpu().numpy(), ref) <= TOL64
+        assert abs(plan.info()["removed_mean"] - m) <= 1e-14
+        phi = plan.solve_divergence(to_dev(u), to_dev(v), to_dev(w), 0.3)
+        ref, _ = oracle.solve(rhs, 2 * np.pi, 1.7, yf, bc=bc)
+        assert rel(phi.cpu().numpy(), ref) <= TOL64
+        plan.close()
