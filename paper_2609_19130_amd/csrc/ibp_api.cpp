@@ -1423,7 +1423,8 @@ hipError_t run_xr2c(const ibp_plan_s* p, int mode, const XArgs<T>& a, hipStream_
   // register Bluestein: the FP64 right-hand side pass (the others keep the
   // LDS kernels, whose norm partials and residual modes it does not carry)
   if constexpr (sizeof(T) == 8)
-    if (p->xbm && mode == XM_PLAIN && p->chunk <= 0) return launch_xblu_r2c<T>(with_xblu(p, a), p->xbm, s);
+    if (p->xbm && blu_built<T>(p->xbm) && mode == XM_PLAIN && p->chunk <= 0)
+      return launch_xblu_r2c<T>(with_xblu(p, a), p->xbm, s);
   if (mode == XM_RESID_ONLY) {
     XArgs<T> b = a;
     b.row_begin = 0;
@@ -1442,7 +1443,7 @@ hipError_t run_xc2r(const ibp_plan_s* p, int mode, const XArgs<T>& a, hipStream_
   if (p->xfast) return launch_xc2r_fast<T>(mode, a, s);
   if constexpr (sizeof(T) == 8)
     if (p->mxon) return mdft::launch_xc2r(mode, a, p->mxi, s);
-  if (p->xbm && p->chunk <= 0) return launch_xblu_c2r<T>(mode, with_xblu(p, a), p->xbm, s);
+  if (p->xbm && blu_built<T>(p->xbm) && p->chunk <= 0) return launch_xblu_c2r<T>(mode, with_xblu(p, a), p->xbm, s);
   return launch_xc2r<T>(mode, p->xsmall, p->xwide, a, s);
 }
 
@@ -1456,7 +1457,7 @@ hipError_t run_zfft(const ibp_plan_s* p, bool inverse, const ZfArgs<T>& a, int n
       return mdft::launch_z(inverse, z, nplanes, s);
     }
   }
-  if (p->zbm) {
+  if (p->zbm && blu_built<T>(p->zbm)) {
     ZfArgs<T> b = a;
     if constexpr (sizeof(T) == 8) {
       b.bc = p->bz64[0]; b.bb = p->bz64[1]; b.bt = p->bz64[2];

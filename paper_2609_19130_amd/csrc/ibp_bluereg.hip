@@ -2,8 +2,10 @@
 // prime factor above 11 (the paper's 501- and 632-point grids: 501 = 3 x 167,
 // 632 = 8 x 79), which the LDS kernels would run as direct-sum stages (up to
 // ~170 complex multiply-adds per value) or, for primes above 256, as their
-// own slower convolution: FP32 lines, and the FP64 lines that no product
-// shape covers (ibp_mdft.hpp; multiples of primes above 256).  A length-n DFT is X_k = w_k sum_j (x_j w_j) conj(w_{k-j}) with
+// own slower convolution: FP32 lines, and the FP64 lines that the product
+// transforms do not take (multiples of primes above 256; long product sums,
+// 128 points and more, where mdft_x_pays and mdft_z_pays say so).  A length-n
+// DFT is X_k = w_k sum_j (x_j w_j) conj(w_{k-j}) with
 // the chirp w_j = exp(-i pi j^2 / n): the sum is a cyclic convolution of
 // length M (a power of two >= 2n - 1, at most 2048), done as two register
 // FFTs of length M (ibp_regfft.hpp) around a pointwise product with the
@@ -208,8 +210,8 @@ __global__ __launch_bounds__(blu_x_threads<M>()) void k_xblu_r2c(XArgs<T> A) {
   sa = row_total<TT>(sa, sh, lr);
   sb = row_total<TT>(sb, sh, lr);
   if (t == 0) {
-    if (live0 && A.rowsum != nullptr) A.rowsum[r0] = sa;
-    if (live1 && A.rowsum != nullptr) A.rowsum[r0 + 1] = sb;
+    if (live0) A.rowsum[r0] = sa;
+    if (live1) A.rowsum[r0 + 1] = sb;
   }
   Cx<T>* L = lds + lr * SS;
   blu_convolve<M, T, SH>(v, t, L, A.bb, A.bt);
@@ -335,13 +337,15 @@ constexpr int blu_z_cols() {
 }
 
 // The M cases of a launcher: f(std::integral_constant<int, M>).
-template <typename F>
+template <typename T, typename F>
 hipError_t blu_dispatch(int M, F&& f) {
+  if constexpr (blu_built<T>(64)) {
+    if (M == 64) return f(std::integral_constant<int, 64>{});
+    if (M == 128) return f(std::integral_constant<int, 128>{});
+    if (M == 256) return f(std::integral_constant<int, 256>{});
+  }
   switch (M) {
     case 32: return f(std::integral_constant<int, 32>{});
-    case 64: return f(std::integral_constant<int, 64>{});
-    case 128: return f(std::integral_constant<int, 128>{});
-    case 256: return f(std::integral_constant<int, 256>{});
     case 512: return f(std::integral_constant<int, 512>{});
     case 1024: return f(std::integral_constant<int, 1024>{});
     case 2048: return f(std::integral_constant<int, 2048>{});
@@ -364,13 +368,13 @@ hipError_t launch_zblu_reg(bool inverse, const ZfArgs<T>& a, int M, int nplanes,
       hipLaunchKernelGGL((k_zblu_reg<T, false, m, C>), grid, dim3(C * (m / kE)), 0, s, a);
     return hipGetLastError();
   };
-  return blu_dispatch(M, go);
+  return blu_dispatch<T>(M, go);
 }
 
 template <typename T>
 hipError_t launch_xblu_r2c(const XArgs<T>& a, int M, hipStream_t s) {
   if (a.nx > 1024 || 2 * a.nx - 1 > M) return hipErrorInvalidValue;
-  return blu_dispatch(M, [&](auto m_) {
+  return blu_dispatch<T>(M, [&](auto m_) {
     constexpr int m = decltype(m_)::value;
     constexpr int NT = blu_x_threads<m>();
     const int RB = 2 * (NT / (m / kE));   // rows per block
@@ -384,7 +388,7 @@ hipError_t launch_xblu_r2c(const XArgs<T>& a, int M, hipStream_t s) {
 template <typename T>
 hipError_t launch_xblu_c2r(int mode, const XArgs<T>& a, int M, hipStream_t s) {
   if (a.nx > 1024 || 2 * a.nx - 1 > M) return hipErrorInvalidValue;
-  return blu_dispatch(M, [&](auto m_) {
+  return blu_dispatch<T>(M, [&](auto m_) {
     constexpr int m = decltype(m_)::value;
     constexpr int NT = blu_x_threads<m>();
     const int RB = 2 * (NT / (m / kE));   // rows per block

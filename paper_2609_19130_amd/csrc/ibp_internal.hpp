@@ -301,6 +301,10 @@ template <typename T>
 hipError_t launch_zblu_reg(bool inverse, const ZfArgs<T>& a, int M, int nplanes, hipStream_t s);
 template <typename T>
 hipError_t launch_xblu_r2c(const XArgs<T>& a, int M, hipStream_t s);
+// Convolution lengths M that it is built for: FP64 lines of 16..128 points take
+// the products (without them, in comparison runs, the LDS kernels).
+template <typename T>
+constexpr bool blu_built(int M) { return sizeof(T) == 4 || M == 32 || M >= 512; }
 template <typename T>
 hipError_t launch_xblu_c2r(int mode, const XArgs<T>& a, int M, hipStream_t s);
 hipError_t launch_x_roundtrip(const RtArgs& a, hipStream_t s);
