@@ -1774,6 +1774,9 @@ ibp_status_t enqueue_mixed(ibp_plan_s* p, const double* rhs, double* phi, hipStr
 // the line-solve coefficient tables are re-padded to the batch's common
 // lanes x rows shape (the largest ny decides it).
 constexpr int kBatchStages = 10;
+// Entries of a stage's prefix offsets of n grids: n + 1, and the total again up
+// to 8 in all (batch_grid_of).
+constexpr int batch_stride(int n) { return n + 1 > 8 ? n + 1 : 8; }
 
 struct ibp_batch_s {
   int device = 0;
@@ -1784,7 +1787,7 @@ struct ibp_batch_s {
   std::vector<unsigned> gens;
   void* dmem = nullptr;
   void* desc = nullptr;      // BatchGrid<T>[count]
-  long* start = nullptr;     // [kBatchStages][count + 1]: prefix offsets of the stage launches (nblk order)
+  long* start = nullptr;     // [kBatchStages][batch_stride(count)]: prefix offsets of the stage launches (nblk order)
   // blocks of the x (narrow, wide family), z (narrow, wide), y (rows per lane
   // K, K/2, K/4) and matrix-product (R2C, C2R, z) stage launches: each stage
   // runs as several launches over the grids of one kind (a grid has no blocks
@@ -1825,9 +1828,9 @@ hipError_t persist_schedule(ibp_batch_s* b, const std::vector<BatchGrid<T>>& hd)
 template <typename T>
 hipError_t batch_apply(ibp_batch_s* b, std::vector<BatchGrid<T>>& hd) {
   const int n = b->count;
-  b->hstart.assign(kBatchStages * (n + 1), 0);
+  b->hstart.assign(kBatchStages * batch_stride(n), 0);
   long* h[kBatchStages];
-  for (int i = 0; i < kBatchStages; ++i) h[i] = b->hstart.data() + i * (n + 1);
+  for (int i = 0; i < kBatchStages; ++i) h[i] = b->hstart.data() + i * batch_stride(n);
   // y launches: the base shape's K, K/2, K/4 rows per lane, with columns per
   // block raised in proportion (same LDS tile, same bytes per block)
   for (int c = 0; c < 3; ++c) {
@@ -1861,7 +1864,10 @@ hipError_t batch_apply(ibp_batch_s* b, std::vector<BatchGrid<T>>& hd) {
       h[4 + c][g + 1] = h[4 + c][g] + (d.yk == b->yKc[c] ? (d.y.Q + M - 1) / M + zero_blocks(d.y) : 0);
     }
   }
-  for (int i = 0; i < kBatchStages; ++i) b->nblk[i] = h[i][n];
+  for (int i = 0; i < kBatchStages; ++i) {
+    b->nblk[i] = h[i][n];
+    for (int k = n + 1; k < batch_stride(n); ++k) h[i][k] = h[i][n];
+  }
   hipError_t e = hipMemcpy(b->desc, hd.data(), n * sizeof(BatchGrid<T>), hipMemcpyHostToDevice);
   if (e == hipSuccess)
     e = hipMemcpy(b->start, b->hstart.data(), b->hstart.size() * sizeof(long), hipMemcpyHostToDevice);
@@ -2080,7 +2086,7 @@ ibp_status_t batch_build(ibp_batch_s* b) {
   // device memory: descriptors | prefix offsets | padded a, c tables | partials
   std::vector<size_t> o_part(n);
   const size_t o_start = align256(n * sizeof(BatchGrid<T>));
-  const size_t o_tab = o_start + align256(kBatchStages * (n + 1) * sizeof(long));
+  const size_t o_tab = o_start + align256(kBatchStages * batch_stride(n) * sizeof(long));
   size_t bytes = o_tab + align256((size_t)n * 2 * PK * sizeof(T));
   for (int g = 0; g < n; ++g) {
     const ibp_plan_s* p = b->plans[g];
@@ -2170,7 +2176,7 @@ ibp_status_t batch_enqueue(ibp_batch_s* b, const double* const* rhs, double* con
   }
   const BatchGrid<T>* d = static_cast<const BatchGrid<T>*>(b->desc);
   const long* st[kBatchStages];
-  for (int i = 0; i < kBatchStages; ++i) st[i] = b->start + i * (n + 1);
+  for (int i = 0; i < kBatchStages; ++i) st[i] = b->start + i * batch_stride(n);
   const bool mixed = b->prec == IBP_MIXED;
   for (ibp_plan_t p : b->plans) {
     p->last_stream = s;

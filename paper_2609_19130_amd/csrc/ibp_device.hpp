@@ -504,9 +504,18 @@ __device__ __forceinline__ void block_reduce(double (&v)[NV], const bool (&is_ma
 
 // ---------------------------------------------------------------- batched launches
 // Grid of block b of a batched launch: the largest g with start[g] <= b
-// (start ascending, start[0] = 0).  64 entries a load; every wave calls it
-// with all its lanes.
-__device__ __forceinline__ int batch_grid_of(const long* start, int count, long b) {
+// (start ascending, start[0] = 0, the total from start[count] on, 8 entries at
+// least).  Up to 8 grids: one run of scalar loads (two grids of 400..512
+// points, z pass 836 us; one vector load a lane with a ballot 856; with 64
+// grids the other way round: two rounds of scalar loads 5.99 ms a mixed solve,
+// the ballot 5.75).  Every wave calls it with all its lanes.
+__device__ __forceinline__ int batch_grid_of(const long* __restrict__ start, int count, long b) {
+  if (count <= 8) {
+    int g = 0;
+#pragma unroll
+    for (int k = 1; k < 8; ++k) g += (int)start[k] <= (int)b ? 1 : 0;
+    return g;
+  }
   int g = -1;
   for (int i0 = 0; i0 < count; i0 += kWave) {
     const int i = i0 + (int)(threadIdx.x & (kWave - 1));

@@ -333,3 +333,32 @@ def test_tuning_cache(monkeypatch, tmp_path):
         o.close()
     for p in plans + [a, b]:
         p.close()
+
+
+@pytest.mark.parametrize("dims", [[(126, 70, 132)], [(126, 70, 132), (256, 80, 10)],
+                                  [(8 + 2 * i, 66 + i, 10 + i % 3) for i in range(4)] + [(154, 90, 121)] * 3,
+                                  [(20 + 4 * i, 70 - i, (16, 18, 20, 22)[i % 4]) for i in range(8)],
+                                  [(20 + 4 * i, 70 - i, (16, 18, 20, 22)[i % 4]) for i in range(8)] + [(56, 100, 48)]],
+                         ids=["1", "2-general", "7-general", "8-products", "9-products"])
+def test_batch_sizes_on_both_sides_of_the_grid_search(dims):
+    """Grid search by scalar loads (up to 8 grids) and by ballot; batches
+    without and with matrix-product lines (a persistent kernel each): staged
+    and persistent alike to the bit, and every grid against its single solve."""
+    plans, rhs = [], []
+    for i, (nx, ny, nz) in enumerate(dims):
+        f = np.random.default_rng(90 + i).standard_normal((ny, nz, nx))
+        plans.append(ibp.Plan(nx, ny, nz, 2 * np.pi, 1.3, synth.tanh_faces(ny, 2.0)))
+        rhs.append(to_dev(f))
+    b = ibp.Batch(plans)
+    b.set_persistent(False)
+    staged = b.solve(rhs)
+    b.set_persistent(True)
+    out = b.solve(rhs)
+    torch.cuda.synchronize()
+    for i, (p, r) in enumerate(zip(plans, rhs)):
+        assert torch.equal(out[i], staged[i]), dims[i]
+        single = p.solve(r)
+        assert float(torch.linalg.vector_norm(single - out[i]) / torch.linalg.vector_norm(single)) <= TOL64, dims[i]
+    b.close()
+    for p in plans:
+        p.close()
