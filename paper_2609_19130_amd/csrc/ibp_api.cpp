@@ -1794,6 +1794,7 @@ struct ibp_batch_s {
   // in the others)
   long nblk[kBatchStages] = {0};
   size_t mlds[3] = {0, 0, 0};   // largest tile of the R2C, C2R and z matrix-product launches
+  bool products() const { return mlds[0] != 0 || mlds[2] != 0; }
   int yKc[3] = {0, 0, 0}, yMc[3] = {0, 0, 0};   // rows per lane and columns per block of the y launches
   int yP = 32, yK = 2, yM = 8;
   int xdiv = 1, zdiv = 1;    // x rows and z columns per block: the largest tile's, divided by these
@@ -1984,7 +1985,7 @@ hipError_t persist_setup(ibp_batch_s* b) {
     return hipSuccess;
   }
   int per_cu = 0, ncu = 0;
-  e = persist_blocks_per_cu<T>(b->wide, b->yP, b->yK, &per_cu);
+  e = persist_blocks_per_cu<T>(b->wide, b->products(), b->yP, b->yK, &per_cu);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, b->device);
   if (e != hipSuccess) return e;
   if (per_cu < 1 || ncu < 1) {
@@ -2184,7 +2185,7 @@ ibp_status_t batch_enqueue(ibp_batch_s* b, const double* const* rhs, double* con
     p->info_ctl = p->ctl;
   }
   if (b->persist) {   // every stage of every grid in one launch
-    IBP_HIP(launch_persist<T>(b->wide, b->yP, b->yK, b->pargs, P, b->persist_blocks, s));
+    IBP_HIP(launch_persist<T>(b->wide, b->products(), b->yP, b->yK, b->pargs, P, b->persist_blocks, s));
     return IBP_SUCCESS;
   }
   // each transform stage: the narrow-family launch, the wide one, then the

@@ -503,9 +503,9 @@ struct PersistArgs {
 // Lanes and rows per lane the persistent kernel is built for.
 bool persist_shape_supported(int P, int K);
 template <typename T>
-hipError_t persist_blocks_per_cu(bool wide, int P, int K, int* per_cu);
+hipError_t persist_blocks_per_cu(bool wide, bool products, int P, int K, int* per_cu);
 template <typename T>
-hipError_t launch_persist(bool wide, int P, int K, const PersistArgs& a, const BatchPtrs& p, int blocks,
+hipError_t launch_persist(bool wide, bool products, int P, int K, const PersistArgs& a, const BatchPtrs& p, int blocks,
                           hipStream_t s);
 
 // Stages of a batched solve; each launcher covers every grid in one launch.

@@ -20,6 +20,8 @@
 // dependency points to an earlier segment of the same queue, so the wait of
 // a claimed item always ends; it is also bounded, raising the grid's error
 // flag instead of hanging.
+#pragma once
+
 #include "ibp_internal.hpp"
 #include "ibp_mbatch.hpp"
 #include "ibp_xz_kernels.hpp"
@@ -28,13 +30,14 @@
 namespace ibp {
 
 // Waves per SIMD the persistent kernel is compiled for: at 2 (up to 256
-// VGPRs) no instance spills; at 3 every instance spills 120-530 bytes and
-// the 64-grid batch still runs 5% (FP64) and 11% (mixed) faster.
+// VGPRs) few instances spill; at 3 every one does (FP64 36..568 bytes a lane,
+// with products 444..796, mixed forms 160..308) and the 64-grid batch still
+// ran 5% (FP64) and 11% (mixed) faster.
 #ifndef IBP_PERSIST_WAVES
 #define IBP_PERSIST_WAVES 3
 #endif
 
-template <typename T, bool W, int P, int K0>
+template <typename T, bool MD, int P, int K0>
 struct PersistShape {
   static constexpr int TLX = sizeof(T) == 8 ? kTileX64s : kTileX32s;
   static constexpr int TLZ = sizeof(T) == 8 ? kTileZ64s : kTileZ32s;
@@ -43,14 +46,17 @@ struct PersistShape {
   static constexpr long bz = (long)(TLZ + 64) * sizeof(Cx<T>);
   static constexpr long by = ytile_slots<M, P, K0>() * (long)sizeof(Cx<T>);
   static constexpr long bg = bx > bz ? (bx > by ? bx : by) : (bz > by ? bz : by);
-  // FP64: the matrix-product tiles too
-  static constexpr long buf = sizeof(T) == 8 && (long)mdft::kBatchLds > bg ? (long)mdft::kBatchLds : bg;
+  // with matrix-product tiles
+  static constexpr long buf = MD && (long)mdft::kBatchLds > bg ? (long)mdft::kBatchLds : bg;
 };
 
 // One tile of a matrix-product stage.  A function of its own: its bodies are
 // then built once and not once per kernel instance.  Arguments arrive in
 // vector registers; they are the same in every lane and are made uniform
-// again (the bodies hold barriers and scalar branches).
+// again (the bodies hold barriers and scalar branches).  One tile an item: a
+// loop over tiles keeps the next one in flight, in registers that this
+// function does not have (scratch 508 -> 936 bytes, 64 uneven grids 3.95 ->
+// 4.8..5.8 ms with one, two or four tiles).
 typedef __attribute__((address_space(3))) char lds_char;
 template <typename P>
 __device__ __forceinline__ P* uniform_ptr(P* p) {
@@ -87,7 +93,7 @@ __device__ __forceinline__ int persist_segment(const PersistSeg* seg, int lo, in
 template <typename T, bool W, int MODE>
 __device__ __forceinline__ void pb_x(const BatchGrid<T>* D, int g, const double* f, double* phi, int iter, long blk,
                                   Cx<T>* buf, double* sh) {
-  using S = PersistShape<T, W, 32, 4>;
+  using S = PersistShape<T, false, 32, 4>;
   XArgs<T> a = D[g].x;
   a.f = f;
   a.phi = phi;
@@ -101,7 +107,7 @@ __device__ __forceinline__ void pb_x(const BatchGrid<T>* D, int g, const double*
 
 template <typename T, bool W, bool INV>
 __device__ __forceinline__ void pb_z(const BatchGrid<T>* D, int g, int check_done, long blk, Cx<T>* buf) {
-  using S = PersistShape<T, W, 32, 4>;
+  using S = PersistShape<T, false, 32, 4>;
   ZfArgs<T> z = D[g].z;
   z.check_done = check_done;
   const int ncb = D[g].zcolblocks;
@@ -118,7 +124,7 @@ __device__ __forceinline__ void pb_y(const BatchGrid<T>* D, int g, int flags, in
   zr.mixed = mixed;
   zr.iter = iter;
   zr.final_pass = 0;
-  ytri_body<T, T, M, P, K>(y, zr, blk, buf);
+  ytri_body<T, T, M, P, K, false, false, true>(y, zr, blk, buf);
 }
 
 template <typename T>
@@ -131,14 +137,14 @@ __device__ __forceinline__ void pb_check(const BatchGrid<T>* D, int g, int flags
   check_body<kThreads>(zr, sh);
 }
 
-template <typename T, bool W, int P, int K0>
+template <typename T, bool W, bool MD, int P, int K0>
 __device__ __forceinline__ void persist_item(const PersistArgs& A, const BatchPtrs& Pt, const PersistSeg& sg,
                                              long blk, char* smem, double* sh) {
-  using S = PersistShape<T, W, P, K0>;
+  using S = PersistShape<T, MD, P, K0>;
   const BatchGrid<T>* D = static_cast<const BatchGrid<T>*>(A.grids);
   const int g = sg.g;
   Cx<T>* buf = reinterpret_cast<Cx<T>*>(smem);
-  if constexpr (sizeof(T) == 8) {
+  if constexpr (MD) {
     const mdft::BatchPlan& md = D[g].md;
     const bool x = sg.kind == PK_XR2C || sg.kind == PK_XC2R, z = sg.kind == PK_ZF || sg.kind == PK_ZI;
     if ((x && __builtin_amdgcn_readfirstlane(md.f.M.S)) || (z && __builtin_amdgcn_readfirstlane(md.z.M.S))) {
@@ -173,10 +179,10 @@ __device__ __forceinline__ void persist_item(const PersistArgs& A, const BatchPt
   }
 }
 
-template <typename T, bool W, int P, int K0>
+template <typename T, bool W, bool MD, int P, int K0>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(IBP_PERSIST_WAVES)))
 void kp_batch(PersistArgs A, BatchPtrs Pt) {
-  using S = PersistShape<T, W, P, K0>;
+  using S = PersistShape<T, MD, P, K0>;
   __shared__ __attribute__((aligned(16))) char smem[S::buf];
   __shared__ double sh[(kThreads / kWave) * kPartStride];
   __shared__ int claimed;
@@ -224,7 +230,7 @@ void kp_batch(PersistArgs A, BatchPtrs Pt) {
           __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
           verified = si;
         }
-        persist_item<T, W, P, K0>(A, Pt, sg, item - sg.first, smem, sh);
+        persist_item<T, W, MD, P, K0>(A, Pt, sg, item - sg.first, smem, sh);
         __syncthreads();   // the next item re-uses the LDS
         pend_seg = si;
         ++pend;
@@ -253,23 +259,11 @@ void kp_batch(PersistArgs A, BatchPtrs Pt) {
   }
 }
 
-template <typename T, bool W, int P, int K0>
-static hipError_t persist_occ(int* per_cu) {
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      per_cu, reinterpret_cast<const void*>(&kp_batch<T, W, P, K0>), kThreads, 0);
-}
-
-// (lanes, rows per lane) shapes the persistent kernel is built for: the
-// line-solve shapes of batches whose tallest grid has at most 512 rows
-bool persist_shape_supported(int P, int K) {
-  return (P == 32 && (K == 4 || K == 8 || K == 12)) || (P == 64 && K == 8);
-}
-
-template <typename T>
-hipError_t persist_blocks_per_cu(bool wide, int P, int K, int* per_cu) {
-  *per_cu = 0;
-#define IBP_PERSIST_CASE(PP, KK)                                                          \
-  if (P == PP && K == KK) return wide ? persist_occ<T, true, PP, KK>(per_cu) : persist_occ<T, false, PP, KK>(per_cu);
+// f(kernel) for a line-solve shape that it is built for (persist_shape_supported)
+template <typename T, bool MD, typename F>
+hipError_t persist_pick(bool wide, int P, int K, F&& f) {
+#define IBP_PERSIST_CASE(PP, KK) \
+  if (P == PP && K == KK) return wide ? f(kp_batch<T, true, MD, PP, KK>) : f(kp_batch<T, false, MD, PP, KK>);
   IBP_PERSIST_CASE(32, 4)
   IBP_PERSIST_CASE(32, 8)
   IBP_PERSIST_CASE(32, 12)
@@ -278,26 +272,21 @@ hipError_t persist_blocks_per_cu(bool wide, int P, int K, int* per_cu) {
   return hipErrorInvalidValue;
 }
 
-template <typename T>
-hipError_t launch_persist(bool wide, int P, int K, const PersistArgs& a, const BatchPtrs& p, int blocks,
+template <typename T, bool MD>
+hipError_t persist_occupancy(bool wide, int P, int K, int* per_cu) {
+  *per_cu = 0;
+  return persist_pick<T, MD>(wide, P, K, [&](auto kern) {
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, reinterpret_cast<const void*>(kern), kThreads, 0);
+  });
+}
+
+template <typename T, bool MD>
+hipError_t persist_launch(bool wide, int P, int K, const PersistArgs& a, const BatchPtrs& p, int blocks,
                           hipStream_t s) {
-  auto go = [&](auto kern) {
+  return persist_pick<T, MD>(wide, P, K, [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kThreads), 0, s, a, p);
     return hipGetLastError();
-  };
-#define IBP_PERSIST_CASE(PP, KK) \
-  if (P == PP && K == KK) return wide ? go(kp_batch<T, true, PP, KK>) : go(kp_batch<T, false, PP, KK>);
-  IBP_PERSIST_CASE(32, 4)
-  IBP_PERSIST_CASE(32, 8)
-  IBP_PERSIST_CASE(32, 12)
-  IBP_PERSIST_CASE(64, 8)
-#undef IBP_PERSIST_CASE
-  return hipErrorInvalidValue;
+  });
 }
-
-template hipError_t persist_blocks_per_cu<double>(bool, int, int, int*);
-template hipError_t persist_blocks_per_cu<float>(bool, int, int, int*);
-template hipError_t launch_persist<double>(bool, int, int, const PersistArgs&, const BatchPtrs&, int, hipStream_t);
-template hipError_t launch_persist<float>(bool, int, int, const PersistArgs&, const BatchPtrs&, int, hipStream_t);
 
 }  // namespace ibp

@@ -375,7 +375,7 @@ __device__ __forceinline__ void ytri_coef(const YArgs<T, U>& A, long q0, YCoef<U
   if (C.zero) C.L = U(1);   // singular (0,0): solved in FP64 by the (0,0)-mode blocks, zeroed here
 }
 
-template <typename T, typename U, int M, int P, int K, bool OUT64 = false, bool ADD = false>
+template <typename T, typename U, int M, int P, int K, bool OUT64 = false, bool ADD = false, bool TIGHT = (K > 16)>
 __device__ __forceinline__ void ytri_solve(const YArgs<T, U>& A, long q0, Cx<T>* tile, const YCoef<U, K>& C,
                                            const Cx<double> (*old)[K] = nullptr);
 
@@ -386,7 +386,7 @@ __device__ __forceinline__ void ytri_solve(const YArgs<T, U>& A, long q0, Cx<T>*
 // inverse z pass, which transforms all kz of one kx group per block and runs
 // its groups in descending order, then starts on the groups written last,
 // still in the Infinity Cache.  Every thread of the block calls it.
-template <typename T, typename U, int M, int P, int K, bool OUT64 = false, bool ADD = false>
+template <typename T, typename U, int M, int P, int K, bool OUT64 = false, bool ADD = false, bool PACKED = false>
 __device__ __forceinline__ void ytri_body(const YArgs<T, U>& A, const ZeroArgs& Z, long blk, Cx<T>* tile,
                                           bool kx_major = false) {
   constexpr int NT = M * P;
@@ -431,8 +431,8 @@ __device__ __forceinline__ void ytri_body(const YArgs<T, U>& A, const ZeroArgs& 
   const int lm = threadIdx.x % M, row0 = threadIdx.x / M;
   Cx<T> ld[K];
   ytri_load<T, U, M, P, K>(A, q0, lm, row0, ld);
-  constexpr bool kEarly = K <= 12;
   YCoef<U, K> C;
+  constexpr bool kEarly = K <= 12 && !PACKED;
   if constexpr (kEarly) ytri_coef<T, U, M, P, K>(A, q0, C);
   if constexpr (ADD) {
     // the FP64 values the solution is added to, loaded with the input (the
@@ -455,7 +455,7 @@ __device__ __forceinline__ void ytri_body(const YArgs<T, U>& A, const ZeroArgs& 
     ytri_stage<T, M, P, K>(A.ny, lm, row0, ld, tile);
     __syncthreads();
     if constexpr (!kEarly) ytri_coef<T, U, M, P, K>(A, q0, C);
-    ytri_solve<T, U, M, P, K, OUT64>(A, q0, tile, C);
+    ytri_solve<T, U, M, P, K, OUT64, false, (K > 16) || PACKED>(A, q0, tile, C);
   }
 }
 
@@ -463,7 +463,7 @@ __device__ __forceinline__ void ytri_body(const YArgs<T, U>& A, const ZeroArgs& 
 // the solution is written in FP64 to A.out64; `tile` is then the first half
 // of an LDS buffer of ytile_slots FP64 entries, re-used as their FP64 staging
 // once every lane has read its staged rows.
-template <typename T, typename U, int M, int P, int K, bool OUT64, bool ADD>
+template <typename T, typename U, int M, int P, int K, bool OUT64, bool ADD, bool TIGHT>
 __device__ __forceinline__ void ytri_solve(const YArgs<T, U>& A, long q0, Cx<T>* tile, const YCoef<U, K>& C,
                                            const Cx<double> (*old)[K]) {
   constexpr int PS = K * M + 1;   // LDS slots per partition
@@ -527,10 +527,11 @@ __device__ __forceinline__ void ytri_solve(const YArgs<T, U>& A, long q0, Cx<T>*
     // eps_{-1} = 1 (the value beyond the lower wall does not depend on X_0)
     const U eA = lane_move<kWaveShr1>(mA), eB = lane_move<kWaveShr1>(mB);
     const U eC = lane_move<kWaveShr1>(mC), eD = lane_move<kWaveShr1>(mD);
-    // 24 rows: their shifts (L, or 1 past ny) are formed again below, since kept
-    // over both sweeps they spill (FP32 spectra with FP64 arithmetic, scratch
-    // 440 -> 356 bytes, 256 x 1025 x 256: 239 -> 201 us)
-    if constexpr (K > 16 && sizeof(U) == 8) asm volatile("" : "+v"(Lr));
+    // the rows' shifts (L, or 1 past ny) are formed again below where registers
+    // are short, since kept over both sweeps they spill (24 rows, FP32 spectra
+    // with FP64 arithmetic: scratch 440 -> 356 bytes, 256 x 1025 x 256 239 ->
+    // 201 us)
+    if constexpr (TIGHT && sizeof(U) == 8) asm volatile("" : "+v"(Lr));
     U e = (eA + eB) / (eC + eD);
     if (p == 0) e = U(1);
     // with the pivots known, keep a_j / D_j, c_j / D_j and F_j / D_j only
