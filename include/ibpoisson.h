@@ -193,9 +193,13 @@ ibp_status_t ibp_solve_scratch(ibp_plan_t plan, const double* rhs, double* phi, 
  * Callers that capture graphs from the first call build the batch
  * explicitly with ibp_batch_create.  Otherwise the plans are solved one after
  * another on `stream`.  The batched stages transform every grid with
- * matrix products (FP64, lengths S P with S <= 8) or the general mixed-radix
- * kernels, so results can differ from ibp_solve's in the last bits, e.g. for
- * grids that ibp_solve transforms with its power-of-two kernels. */
+ * matrix products (FP64, lengths whose shape S P of fewest products has
+ * S <= 8) or the general mixed-radix kernels, and solve the lines in one
+ * staged kernel, so results can differ from ibp_solve's in the last bits,
+ * e.g. for lengths that ibp_solve transforms with its power-of-two kernels or
+ * with products of S > 8, for FP64 grids of 513..768 or 1025..1536 rows, which
+ * it solves in registers, and for the shorter grids of a batch whose tallest
+ * has more than 256 rows (another order of their line solves' scans). */
 ibp_status_t ibp_solve_batched(const ibp_plan_t* plans, int count, const double* const* rhs,
                                double* const* phi, hipStream_t stream);
 
@@ -243,7 +247,11 @@ ibp_status_t ibp_batch_destroy(ibp_batch_t batch);
 /* ---------------------------------------------------------------- autotuning
  * Work splits chosen by timing: how many rows, columns or lines each block
  * of a stage takes.  They change which block computes what, never the
- * arithmetic, so solutions are bitwise the same under every choice. */
+ * arithmetic, so solutions are bitwise the same under every choice.  A split
+ * of kernels that the plan or batch does not run is without effect: line-solve
+ * columns for FP64 plans of 513..768 or 1025..1536 rows, rows and tiles of
+ * transforms that run as matrix products or in registers (a plan's products
+ * along z take half lines from zdiv = 2 on, a batch's do not). */
 typedef struct {
   int xdiv;          /* x-stage rows per block = the largest tile's / xdiv (batches, FP64) */
   int zdiv;          /* z-stage columns per block = the largest tile's / zdiv (general z transform) */
@@ -261,8 +269,8 @@ typedef struct {
 
 /* Time solves of rhs into phi (device pointers as in ibp_solve; phi is
  * overwritten with the solution) over the plan's tunable configurations and
- * keep the fastest: the LDS tile (small or large) of the general x and z
- * transforms, z columns and line-solve columns per block.  Synchronises
+ * keep the fastest: the LDS tile (small or large) of the general x (IBP_FP64)
+ * and z transforms, z columns and line-solve columns per block.  Synchronises
  * `stream`; not for use under graph capture.
  *
  * Tuning cache: when the environment variable IBP_TUNE_CACHE names a file,

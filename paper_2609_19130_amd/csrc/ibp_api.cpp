@@ -2021,15 +2021,16 @@ hipError_t persist_setup(ibp_batch_s* b) {
   a.chunk = 8;
   for (int i = 0; i < kMaxXcc; ++i) a.xcc_queue[i] = m.queue[i];
   for (int g = 0; g < b->count; ++g) a.err[g] = b->plans[g]->fctl + kFctlError;
-  // measured slower than one launch per stage on the 64-grid batch (4.6 ms
-  // against 2.9 ms FP64): opt-in (ibp_batch_set_persistent) or chosen by the
+  // measured slower than one launch per stage on the 64-grid batch (3.9 ms
+  // against 1.7 ms FP64): opt-in (ibp_batch_set_persistent) or chosen by the
   // batch autotuner when it is faster
   b->persist = false;
   return hipSuccess;
 }
 
-// Matrix-product tiles of one grid of a batch (BatchPlan), where its lengths
-// have a shape with S <= 8 whose tiles fit.
+// Matrix-product tiles of one grid of a batch (BatchPlan), for lengths whose
+// shape of fewest products has S <= 8 and tiles that fit; the others (such as
+// 126, 132 and 256) keep the general kernels.
 void batch_mdft(const ibp_plan_s* p, mdft::BatchPlan& md, const ZfArgs<double>& z) {
   const char* on = getenv("IBP_MDFT");
   if (on && atoi(on) == 0) return;
@@ -2524,7 +2525,9 @@ bool plan_x_tile_choice(const ibp_plan_s* p) {
 bool plan_z_tile_choice(const ibp_plan_s* p) { return !p->zfast && p->nz > 1 && z_small(p->fpz, p->nz); }
 
 // A plan configuration: x and z tiles (where the plan may choose), z columns
-// per block, line-solve columns per block.  None changes the arithmetic.
+// per block, line-solve columns per block.  None changes the arithmetic: FP64
+// rows of the register line solve ignore the columns (launch_ytri), and the
+// mixed forms' x tile, which orders their norm partials, is not a choice.
 void apply_plan_cfg(ibp_plan_s* p, const TuneCfg& c) {
   if (c.xsmall >= 0 && plan_x_tile_choice(p)) {
     p->xsmall = c.xsmall != 0;

@@ -11,10 +11,10 @@
 // and, for even P, x_{P/2} stand alone),
 //   A_q = sum_r s_r cos(2 pi q r / P),  B_q = sum_r d_r sin(2 pi q r / P),
 //   y_q = A_q - i B_q,  y_{P-q} = A_q + i B_q,   q <= P/2,
-// so a real product of (P/2 + 1)^2 entries serves cosine and sine each: n = 320
-// = 16 x 20 takes 77 flops a value in the products, 632 = 8 x 79 takes 194
-// and 501 = 3 x 167 takes 386, against 480 in the time that HBM needs for the
-// value's 32 bytes.  The matrix is never stored: a lane steps through
+// so a real product of (P/2 + 1)^2 entries serves cosine and sine each: padded to
+// the steps below, n = 320 = 16 x 20 takes 102 flops a value in the products,
+// 632 = 8 x 79 takes 194 and 501 = 3 x 167 takes 405, against 480 in the time
+// that a large copy needs for the value's 32 bytes.  The matrix is never stored: a lane steps through
 // W_P^{q r} in a table of its P roots (LDS).
 //
 // Real rows: R2C takes two rows a, b as one complex value through the S-point
@@ -136,7 +136,8 @@ template <bool INV, typename T> struct Dft<16, INV, T> : DftAB<4, 4, INV, T> {};
 
 // Twiddle factors W^{j k}, k = 1 .. S-1, of one task, kept in registers over
 // its tiles: up to 4 are all read from the table; longer sets hold W^{b j}
-// (b < 4) and W^{4 a j} and form the rest as one product each.
+// (b < 4) and W^{4 a j} and form the rest as one rounded product each, which
+// adds 2 to 4 % to a transform's error at S > 4 (emulated in double).
 template <int S, bool INV>
 struct Twiddle {
   static constexpr int NL = S < 4 ? S : 4, NH = S <= 4 ? 1 : (S + 3) / 4;
