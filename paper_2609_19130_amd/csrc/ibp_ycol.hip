@@ -13,7 +13,7 @@
 // only the coefficients and runs while the field's loads are in flight.
 // Bound by memory.  Measured, staged -> here, us: 384 x 600 x 400 460 -> 382,
 // 1024 x 768 x 1024 3345 -> 2760 (4.7 TB/s), 632 x 1263 x 632 3074 -> 2081
-// (3.9), 500 x 1500 x 400 1553 -> 1167.  Where the staged kernel has two or
+// (with 32-bit indices since 1945, 4.2 TB/s), 500 x 1500 x 400 1553 -> 1167.  Where the staged kernel has two or
 // more blocks per compute unit it stays: 61 against 71 us at 256^3, 367
 // against 381 at 512 x 384 x 512, 922 against 989 at 501 x 1001 x 501.
 #include "ibp_internal.hpp"
